@@ -6,6 +6,8 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <set>
+#include <utility>
 
 #include "host.h"
 #include "launch.h"
@@ -379,6 +381,19 @@ static void* noalloc_scratch_ptr() {
   return g_noalloc_ptr[dev];
 }
 
+hipError_t raise_lds_limit(const void* k, int bytes) {
+  static std::mutex mu;
+  static std::set<std::pair<int, const void*>> done;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  std::lock_guard<std::mutex> lock(mu);
+  if (done.count({dev, k})) return hipSuccess;
+  e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.insert({dev, k});
+  return e;
+}
+
 static void product(ffx_matrix M, bool trans, int s, uint32_t alpha, const void* X, int64_t ldx, uint32_t beta,
                     void* Y, int64_t ldy, ffx_dtype dt, hipStream_t st) {
   if (!check_product(M, trans, s, alpha, X, ldx, beta, Y, ldy, dt)) return;
@@ -417,14 +432,22 @@ static void product(ffx_matrix M, bool trans, int s, uint32_t alpha, const void*
     FFX_HIP(e);
     return;
   }
-  // the scatter form of A^T, with 64-bit integer atomics into a temporary
+  // A^T from the entries of A: binned by output panel where that pays and its scratch is there, else
+  // with 64-bit integer atomics into a temporary
   auto scatter = [&](const void* xs, int64_t ldxs, void* ys, int64_t ldys) {
     warm_pool(st);
-    unsigned long long* acc = nullptr;
-    size_t bytes = (size_t)nout * s * sizeof(uint64_t);
-    if (hipMallocAsync((void**)&acc, bytes, st) != hipSuccess) fail(FFX_ENOMEM, "hipMallocAsync of %zu bytes", bytes);
-    hipError_t e = launch_transpose_scatter(M->md.small(), M->A.dm, dt, xs, ldxs, ys, ldys, s, alpha, beta, acc, st);
-    (void)hipFreeAsync(acc, st);
+    const Encoded& E = M->A;
+    const TransposeInfo I{E.nnz, E.t_recs, E.t_batches};
+    void* tmp = nullptr;
+    size_t bytes = transpose_scratch_bytes(E.dm, I, s, true);
+    const bool binned = bytes && hipMallocAsync(&tmp, bytes, st) == hipSuccess;
+    if (!binned) {
+      if (bytes) (void)hipGetLastError();
+      bytes = transpose_scratch_bytes(E.dm, I, s, false);
+      if (hipMallocAsync(&tmp, bytes, st) != hipSuccess) fail(FFX_ENOMEM, "hipMallocAsync of %zu bytes", bytes);
+    }
+    hipError_t e = launch_transpose(E.dm, I, dt, xs, ldxs, ys, ldys, s, alpha, beta, tmp, binned, st);
+    (void)hipFreeAsync(tmp, st);
     FFX_HIP(e);
   };
   if (M->perm) {  // gather x (and y when beta != 0) into the stored order, scatter y back

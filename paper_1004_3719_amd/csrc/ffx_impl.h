@@ -68,6 +68,16 @@ __host__ __device__ inline uint32_t tile_kind(uint32_t k) { return k & 0xF; }
 __host__ __device__ inline uint32_t tile_nd(uint32_t k) { return (k >> 8) & 0xFF; }
 __host__ __device__ inline uint32_t tile_rows(uint32_t k) { return k >> 16; }
 
+// A batch of the transposed product: at most TB_MAX entries of one tile, either n of its 256-word
+// chunks from `first` on or (TB_BAND) n of its diagonals from `first` on. Its records start at rec0
+// (even).
+constexpr uint32_t TB_MAX = 2048;
+constexpr uint32_t TB_BAND = 1u << 31;
+struct TBatch {
+  uint32_t tile, first, n, rec0;
+};
+static_assert(sizeof(TBatch) == 16, "batch layout");
+
 // Everything a kernel needs about one encoded matrix (passed by value).
 struct DevMat {
   const Tile* tiles;
@@ -81,6 +91,7 @@ struct DevMat {
   const int32_t* boffs;  // band diagonal offsets (column - row)
   const uint32_t* ltiles;// STREAM tiles flagged TF_LONGROWS
   const uint32_t* rowmap;// when not null, row r of the product is written to row rowmap[r] of Y
+  const TBatch* tbatch;  // batches of the transposed product
   uint32_t nltiles;
   uint32_t ntiles;
   uint32_t nrows, ncols;

@@ -107,6 +107,8 @@ struct Encoded {
   int64_t nrows = 0, ncols = 0;
   int64_t ntiles = 0, max_row_terms = 0, n_band = 0, n_plus = 0, n_minus = 0, nnz = 0;
   int64_t device_bytes = 0, stream_bytes = 0;
+  int64_t t_recs = 0;            // transposed product: records of all batches
+  uint32_t t_batches = 0;        // and the number of batches (0: more records than 32 bits index)
   int64_t max_tile_entries = 0;  // largest STREAM tile (sizes the LDS of a launch)
   std::vector<int32_t> block_fmt;
   std::vector<uint32_t> tile_cost;  // per tile: entry words read (with padding) plus band slots

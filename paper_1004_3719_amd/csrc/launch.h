@@ -93,11 +93,22 @@ hipError_t launch_sequence(int ak, bool only_sell, const DevMat& A, int64_t mte,
                            void* w1, void* u32, uint64_t* p0, uint64_t* p1, int64_t* counter, int batch,
                            hipStream_t st);
 
-// Y = alpha*A^T*X + beta*Y by scattering the entries of A (no stored A^T);
-// acc is workspace of ncols * s uint64.
-hipError_t launch_transpose_scatter(bool small, const DevMat& A, ffx_dtype dt, const void* X, int64_t ldx, void* Y,
-                                    int64_t ldy, int s, uint32_t alpha, uint32_t beta, unsigned long long* acc,
-                                    hipStream_t st);
+// Y = alpha*A^T*X + beta*Y from the entries of A (no stored A^T; transpose.hip). binned: through
+// records sorted by output panel, else by atomics; scratch: transpose_scratch_bytes of device memory
+// (0 for the binned form: this product has none).
+struct TransposeInfo {
+  int64_t nnz;      // stored entries
+  int64_t nrec;     // records of all batches
+  uint32_t nbatch;  // batches (DevMat::tbatch), 0 when there are none
+};
+size_t transpose_scratch_bytes(const DevMat& A, const TransposeInfo& I, int s, bool binned);
+hipError_t launch_transpose(const DevMat& A, const TransposeInfo& I, ffx_dtype dt, const void* X, int64_t ldx, void* Y,
+                            int64_t ldy, int s, uint32_t alpha, uint32_t beta, void* scratch, bool binned,
+                            hipStream_t st);
+
+// Raises the dynamic LDS limit of kernel k on the current device, once per kernel and device (a host
+// call that would otherwise cost a few microseconds per launch).
+hipError_t raise_lds_limit(const void* k, int bytes);
 
 // *first = the smallest flat index k*ldx + c of an entry of the n x s block X
 // outside [0, m-1], or ~0 when there is none (device memory, set by the launch).

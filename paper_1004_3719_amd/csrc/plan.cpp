@@ -468,6 +468,31 @@ void encode(const RCsr& A, const Modulus& md, const PlanOpts& o, hipStream_t str
   for (size_t t = 0; t < H.tiles.size(); ++t)
     if (tile_kind(H.tiles[t].kind) == TK_STREAM && (H.tiles[t].kind & TF_LONGROWS)) ltiles.push_back((uint32_t)t);
   add_part<uint32_t>(offs, total, ltiles.size());
+  // batches of the transposed product: runs of at most 8 chunks, then runs of whole diagonals
+  std::vector<TBatch> tbatch;
+  uint64_t nrec = 0;
+  for (size_t t = 0; t < H.tiles.size(); ++t) {
+    const Tile& T = H.tiles[t];
+    uint32_t chunks = 0, rows = tile_rows(T.kind);
+    if (tile_kind(T.kind) == TK_SELL)
+      for (uint32_t k = 0; k < T.ne; ++k) chunks += H.swidth[T.aux + k];
+    else chunks = (T.ne + WCHUNK - 1) / WCHUNK;
+    auto add = [&](uint32_t first, uint32_t n, uint32_t recs) {
+      tbatch.push_back(TBatch{(uint32_t)t, first, n, (uint32_t)nrec});
+      nrec += (recs + 1) & ~1u;
+    };
+    for (uint32_t c = 0; c < chunks; c += TB_MAX / WCHUNK) {
+      const uint32_t n = std::min<uint32_t>(TB_MAX / WCHUNK, chunks - c);
+      add(c, n, tile_kind(T.kind) == TK_SELL ? n * WCHUNK : std::min<uint32_t>(n * WCHUNK, T.ne - c * WCHUNK));
+    }
+    const uint32_t nd = tile_nd(T.kind), per = TB_MAX / rows;
+    for (uint32_t d = 0; d < nd; d += per) {
+      const uint32_t n = std::min(per, nd - d);
+      add(d, n | TB_BAND, n * rows);
+    }
+  }
+  if (nrec >= UINT32_MAX) tbatch.clear();
+  add_part<TBatch>(offs, total, tbatch.size());
   if (total == 0) total = 256;
   std::vector<unsigned char> host(total, 0);
   auto put = [&](size_t off, const void* src, size_t bytes) { if (bytes) std::memcpy(host.data() + off, src, bytes); };
@@ -487,6 +512,7 @@ void encode(const RCsr& A, const Modulus& md, const PlanOpts& o, hipStream_t str
   put(offs[5], H.perm.data(), H.perm.size() * 4);
   put(offs[6], H.swidth.data(), H.swidth.size() * 4);
   put(offs[9], ltiles.data(), ltiles.size() * 4);
+  put(offs[10], tbatch.data(), tbatch.size() * sizeof(TBatch));
   put(offs[8], H.boffs.data(), H.boffs.size() * 4);
 
   void* dev = nullptr;
@@ -507,6 +533,9 @@ void encode(const RCsr& A, const Modulus& md, const PlanOpts& o, hipStream_t str
   dm.boffs = (const int32_t*)(d + offs[8]);
   dm.ltiles = (const uint32_t*)(d + offs[9]);
   dm.nltiles = (uint32_t)ltiles.size();
+  dm.tbatch = (const TBatch*)(d + offs[10]);
+  out->t_batches = (uint32_t)tbatch.size();
+  out->t_recs = (int64_t)nrec;
   dm.ntiles = (uint32_t)H.tiles.size();
   dm.nrows = (uint32_t)A.nrows;
   dm.ncols = (uint32_t)A.ncols;
