@@ -166,7 +166,7 @@ static ffx_matrix_s* build(const RCsr& A, uint32_t m, const ffx_build_opts* opts
     }
     const RCsr& S = po.reorder ? B : A;
     encode(S, M->md, po, st, &M->A);
-    int64_t maxterms = M->A.max_row_terms;
+    int64_t maxterms = M->A.max_row_terms, max_col = 0;
     if (build_t) {
       RCsr T = transpose(S);
       encode(T, M->md, po, st, &M->AT);
@@ -176,7 +176,8 @@ static ffx_matrix_s* build(const RCsr& A, uint32_t m, const ffx_build_opts* opts
       // the scatter form of A^T sums one column per output: bound by the longest column
       std::vector<int64_t> cnt(S.ncols, 0);
       for (uint32_t c : S.col) cnt[c]++;
-      for (int64_t v : cnt) maxterms = std::max(maxterms, v);
+      for (int64_t v : cnt) max_col = std::max(max_col, v);
+      maxterms = std::max(maxterms, max_col);
     }
     M->chunk = maxterms > b;
     M->compact_x = M->md.small() && (po.compact_x == 1 || (po.compact_x == -1 && A.ncols * 4 > (1 << 20)));
@@ -187,7 +188,7 @@ static ffx_matrix_s* build(const RCsr& A, uint32_t m, const ffx_build_opts* opts
       int dev = 0, ncu = 0;
       FFX_HIP(hipGetDevice(&dev));
       FFX_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-      encode_sg(S, M->md, po.split_pm1, ncu, st, &M->sg);
+      encode_sg(S, M->md, po.split_pm1, ncu, !build_t, max_col, st, &M->sg);
       M->sg.dm.rowmap = M->perm;
     }
     M->A.dm.reduce_every = b;
@@ -436,6 +437,17 @@ static void product(ffx_matrix M, bool trans, int s, uint32_t alpha, const void*
   // with 64-bit integer atomics into a temporary
   auto scatter = [&](const void* xs, int64_t ldxs, void* ys, int64_t ldys) {
     warm_pool(st);
+    if (s == 1 && M->sg.ngroups) {  // one vector on a handle with column-sorted groups
+      void* part = nullptr;
+      const size_t sg_bytes = sg_transpose_scratch(M->sg.dm);
+      if (sg_bytes && hipMallocAsync(&part, sg_bytes, st) == hipSuccess) {
+        hipError_t e = launch_sg_transpose(M->sg.dm, dt, xs, ldxs, ys, ldys, alpha, beta, part, st);
+        (void)hipFreeAsync(part, st);
+        FFX_HIP(e);
+        return;
+      }
+      if (sg_bytes) (void)hipGetLastError();
+    }
     const Encoded& E = M->A;
     const TransposeInfo I{E.nnz, E.t_recs, E.t_batches};
     void* tmp = nullptr;

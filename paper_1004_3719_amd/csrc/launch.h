@@ -106,6 +106,10 @@ hipError_t launch_transpose(const DevMat& A, const TransposeInfo& I, ffx_dtype d
                             int64_t ldy, int s, uint32_t alpha, uint32_t beta, void* scratch, bool binned,
                             hipStream_t st);
 
+// y = alpha*(sum of Q parts) + beta*y mod m: part[q] holds n rows of sp words below 2^32 (Q <= 2^31), s of them used.
+hipError_t launch_t_parts(ffx_dtype dt, uint32_t m, uint64_t mu, int64_t n, const uint32_t* part, uint32_t Q, int s,
+                          int sp, uint32_t alpha, uint32_t beta, void* Y, int64_t ldy, hipStream_t st);
+
 // Raises the dynamic LDS limit of kernel k on the current device, once per kernel and device (a host
 // call that would otherwise cost a few microseconds per launch).
 hipError_t raise_lds_limit(const void* k, int bytes);

@@ -73,7 +73,8 @@ void encode_group(const RCsr& A, int64_t r0, int64_t r1, uint32_t m, bool split,
 
 }  // namespace
 
-void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_groups, hipStream_t st, SgEncoded* out) {
+void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_groups, bool transposed, int64_t max_col,
+               hipStream_t st, SgEncoded* out) {
   out->release();
   if (!md.small()) fail(FFX_EUNSUPPORTED, "column-sorted groups need m <= 65536");
   const int64_t n = A.nrows, nnz = A.nnz();
@@ -104,10 +105,35 @@ void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_grou
     nval += parts[g].val.size();
     nch += parts[g].choff.size();
   }
+  // index of the transposed product: the chunks of each group that hold columns of each panel. Its sums
+  // are 32-bit sums of terms below 3m, so the longest column must keep them below 2^32.
+  const int64_t P = (A.ncols + ((int64_t)1 << SGT_SHIFT) - 1) >> SGT_SHIFT;
+  std::vector<uint2> tindex;
+  if (transposed && max_col * 3 * (int64_t)md.m < ((int64_t)1 << 32) && P * G <= SGT_MAX_INDEX) {
+    tindex.assign((size_t)P * G, make_uint2(0, 0));
+#pragma omp parallel for schedule(dynamic, 1)
+    for (int64_t g = 0; g < G; ++g) {
+      const SgPart& Q = parts[g];
+      for (size_t c = 0; c < Q.choff.size(); ++c) {
+        // sorted: entry e of the chunk at word 4*(e % 64) + e / 64; a padded chunk ends before its first PAD
+        const uint32_t* w = &Q.ent[c * SG_CHUNK];
+        int last = SG_CHUNK - 1;
+        while (last > 0 && (w[4 * (last % 64) + last / 64] >> TAG_SHIFT) == TAG_PAD) --last;
+        const uint32_t lo = (Q.cbase[c] + (w[0] & SG_COL_MASK)) >> SGT_SHIFT,
+                       hi = (Q.cbase[c] + (w[4 * (last % 64) + last / 64] & SG_COL_MASK)) >> SGT_SHIFT;
+        for (uint32_t p = lo; p <= hi; ++p) {
+          uint2& r = tindex[(size_t)p * G + g];
+          if (r.y == 0) r.x = (uint32_t)c;
+          r.y = (uint32_t)c + 1;
+        }
+      }
+    }
+  }
   if (nent >= UINT32_MAX || nval >= UINT32_MAX) fail(FFX_EUNSUPPORTED, "column-sorted encoding exceeds 2^32 words");
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
   const size_t o_g = 0, o_e = o_g + al(G * sizeof(SgGroup)), o_v = o_e + al(nent * 4),
-               o_c = o_v + al(nval * 2 + 16), o_b = o_c + al(nch * 4), total = std::max<size_t>(256, o_b + al(nch * 4));
+               o_c = o_v + al(nval * 2 + 16), o_b = o_c + al(nch * 4), o_t = o_b + al(nch * 4),
+               total = std::max<size_t>(256, o_t + al(tindex.size() * sizeof(uint2)));
   std::vector<unsigned char> host(total, 0);
   std::memcpy(host.data() + o_g, groups.data(), G * sizeof(SgGroup));
   size_t e = 0, v = 0, c = 0;
@@ -122,6 +148,7 @@ void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_grou
     v += P.val.size();
     c += P.choff.size();
   }
+  if (!tindex.empty()) std::memcpy(host.data() + o_t, tindex.data(), tindex.size() * sizeof(uint2));
   if (hipMalloc(&out->alloc, total) != hipSuccess)
     fail(FFX_ENOMEM, "hipMalloc of %zu bytes for the column-sorted groups failed", total);
   if (hipMemcpyAsync(out->alloc, host.data(), total, hipMemcpyHostToDevice, st) != hipSuccess ||
@@ -137,9 +164,11 @@ void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_grou
   M.choff = (const uint32_t*)(d + o_c);
   M.cbase = (const uint32_t*)(d + o_b);
   M.rowmap = nullptr;
+  M.tindex = tindex.empty() ? nullptr : (const uint2*)(d + o_t);
   M.ngroups = (uint32_t)G;
   M.max_rows = max_rows;
   M.nrows = (uint32_t)n;
+  M.ncols = (uint32_t)A.ncols;
   M.m = md.m;
   M.mu = md.mu;
   out->ngroups = G;

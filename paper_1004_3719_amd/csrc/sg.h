@@ -34,6 +34,8 @@ constexpr int SG_CHUNK = 256;
 constexpr uint32_t SG_MAX_ROWS = 1u << 14;  // rows of one group (14-bit row field)
 constexpr uint32_t SG_ROW_SHIFT = 16;
 constexpr uint32_t SG_COL_MASK = 0xFFFFu;
+constexpr uint32_t SGT_SHIFT = 14;          // columns of one panel of the transposed product: 2^14
+constexpr int64_t SGT_MAX_INDEX = 1 << 20;  // (group, panel) pairs up to which its index is kept
 
 struct SgGroup {
   uint32_t row0;     // first row
@@ -50,9 +52,11 @@ struct SgMat {
   const uint32_t* choff;   // per chunk: index of its first general value
   const uint32_t* cbase;   // per chunk: column of its panel's first column
   const uint32_t* rowmap;  // when not null, row r of the product is written to row rowmap[r] of y
+  const uint2* tindex;     // [panel][group]: the chunks (relative to the group) with columns of the panel,
+                           // first and one past the last; null when there is no index
   uint32_t ngroups;
   uint32_t max_rows;       // largest group (sizes the LDS)
-  uint32_t nrows;
+  uint32_t nrows, ncols;
   uint32_t m;
   uint64_t mu;
 };
@@ -62,6 +66,11 @@ struct SgMat {
 // next product's x16 in a chain of products.
 hipError_t launch_sg(const SgMat& G, ffx_dtype dt, const void* x, const uint16_t* x16, void* y, uint32_t alpha,
                      uint32_t beta, hipStream_t st, uint16_t* y16 = nullptr);
+// y = alpha*A^T*x + beta*y from the same groups: x has nrows entries, y ncols. scratch:
+// sg_transpose_scratch bytes of device memory (0: the handle cannot take this form).
+size_t sg_transpose_scratch(const SgMat& G);
+hipError_t launch_sg_transpose(const SgMat& G, ffx_dtype dt, const void* x, int64_t ldx, void* y, int64_t ldy,
+                               uint32_t alpha, uint32_t beta, void* scratch, hipStream_t st);
 // Y = A X over GF(2) for a matrix mod 2 and one bit-packed word per row (32 vectors): X ncols x 1
 // words with stride ldx, Y nrows x 1 with stride ldy (through the row map when there is one).
 hipError_t launch_sg_gf2(const SgMat& G, const uint32_t* X, int64_t ldx, uint32_t* Y, int64_t ldy, hipStream_t st);

@@ -159,10 +159,10 @@ __global__ void k_zero_u64(unsigned long long* p, int64_t n) {
 }
 
 template <typename Tv>
-__device__ inline void finish_row(const DevMat& A, uint64_t sum, uint32_t alpha, uint32_t beta, Tv* y) {
-  const uint32_t r = mod_u64(sum, A.m, A.mu);
+__device__ inline void finish_row(uint32_t m, uint64_t mu, uint64_t sum, uint32_t alpha, uint32_t beta, Tv* y) {
+  const uint32_t r = mod_u64(sum, m, mu);
   const uint32_t yo = beta ? (uint32_t)*y : 0u;
-  *y = (Tv)((alpha == 1 && beta == 0) ? r : axpby(alpha, r, beta, yo, A.m, A.mu));
+  *y = (Tv)((alpha == 1 && beta == 0) ? r : axpby(alpha, r, beta, yo, m, mu));
 }
 
 template <typename Tv>
@@ -171,7 +171,7 @@ __global__ void k_finish_t(DevMat A, const unsigned long long* __restrict__ acc,
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n * s; i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t j = i / s;
     const int c = (int)(i - j * s);
-    finish_row(A, acc[j * sp + c], alpha, beta, Y + j * ldy + c);
+    finish_row(A.m, A.mu, acc[j * sp + c], alpha, beta, Y + j * ldy + c);
   }
 }
 
@@ -386,9 +386,9 @@ __global__ __launch_bounds__(TA_THREADS) void k_t_acc(DevMat A, const Tv* __rest
 
 // y from the parts' residues (at most 16 of them, each below 2^31)
 template <typename Tv>
-__global__ void k_t_parts(DevMat A, const uint32_t* __restrict__ part, uint32_t Q, int s, int sp, uint32_t alpha,
-                          uint32_t beta, Tv* __restrict__ Y, int64_t ldy) {
-  const int64_t n = A.ncols, total = n * s, stride = n * sp;
+__global__ void k_t_parts(uint32_t m, uint64_t mu, int64_t n, const uint32_t* __restrict__ part, uint32_t Q, int s,
+                          int sp, uint32_t alpha, uint32_t beta, Tv* __restrict__ Y, int64_t ldy) {
+  const int64_t total = n * s, stride = n * sp;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t j = i / s;
     const int c = (int)(i - j * s);
@@ -396,11 +396,21 @@ __global__ void k_t_parts(DevMat A, const uint32_t* __restrict__ part, uint32_t 
     uint64_t sum = 0;
 #pragma unroll 4
     for (uint32_t q = 0; q < Q; ++q) sum += a[q * stride];
-    finish_row(A, sum, alpha, beta, Y + j * ldy + c);
+    finish_row(m, mu, sum, alpha, beta, Y + j * ldy + c);
   }
 }
 
 // ------------------------------------------------------------------ host ---
+hipError_t launch_t_parts(ffx_dtype dt, uint32_t m, uint64_t mu, int64_t n, const uint32_t* part, uint32_t Q, int s,
+                          int sp, uint32_t alpha, uint32_t beta, void* Y, int64_t ldy, hipStream_t st) {
+  const dim3 g((unsigned)std::min<int64_t>((n * s + 255) / 256, 8192)), b(256);
+  if (dt == FFX_I32)
+    hipLaunchKernelGGL(k_t_parts<int32_t>, g, b, 0, st, m, mu, n, part, Q, s, sp, alpha, beta, (int32_t*)Y, ldy);
+  else
+    hipLaunchKernelGGL(k_t_parts<int64_t>, g, b, 0, st, m, mu, n, part, Q, s, sp, alpha, beta, (int64_t*)Y, ldy);
+  return hipGetLastError();
+}
+
 static int pow2_at_least(int s) { return s <= 1 ? 1 : s <= 2 ? 2 : s <= 4 ? 4 : s <= 8 ? 8 : 16; }
 
 // Shape of the binned form, or ok = false for the scattered one.
@@ -477,9 +487,8 @@ static hipError_t launch_binned(const DevMat& A, const TransposeInfo& I, const T
     default: e = t_acc_go<K, Tv, 16>(A, I, t, X, ldx, s, rec, off, part, st); break;
   }
   if (e != hipSuccess) return e;
-  const int fb = (int)std::min<int64_t>(((int64_t)A.ncols * s + 255) / 256, 8192);
-  hipLaunchKernelGGL(k_t_parts<Tv>, dim3(fb), dim3(256), 0, st, A, part, t.Q, s, sp, alpha, beta, Y, ldy);
-  return hipGetLastError();
+  return launch_t_parts(sizeof(Tv) == 4 ? FFX_I32 : FFX_I64, A.m, A.mu, A.ncols, part, t.Q, s, sp, alpha, beta, Y, ldy,
+                        st);
 }
 
 template <int K, typename Tv>

@@ -96,3 +96,31 @@ def test_reordered_and_scattered(dev):
     B = powerlaw(900, 700, M31)
     for s in (1, 2, 3, 8, 9):
         check(dev, B, s)
+
+
+@pytest.mark.parametrize("m", [2, 3, 32749, 65521, 65536])
+@pytest.mark.parametrize("shape", [(40_000, 33_001), (16_385, 16_384), (300, 50_000), (70_000, 1), (1, 40_000)])
+def test_column_sorted_groups(dev, m, shape):
+    """One vector on a handle with column-sorted groups: panels of 16,384 columns, chunks across their edges, fewer
+    rows than groups, one column holding everything (whose 32-bit sums the index must refuse when they could wrap)."""
+    print("[case] column sorted", m, shape, flush=True)
+    A = powerlaw(*shape, m=m)
+    check(dev, A, 1, col_sorted=1)
+    check(dev, A, 1, dtype=torch.int32, col_sorted=1, split_pm1=False, axpby=False)
+
+
+@pytest.mark.parametrize("m", [32749, 65536])
+def test_column_sorted_largest_sums(dev, m):
+    """Every entry and x the residue m - 1, in columns at and just above the length the 32-bit sums hold."""
+    from paper_1004_3719_amd import Matrix
+    longest = (2**32 - 1) // (3 * m)
+    for n in (longest, longest + 1):
+        A = synth.Csr(n, 2, np.arange(n + 1, dtype=np.int64), np.zeros(n, np.int32), np.full(n, m - 1, np.int64), m=m)
+        M = Matrix.from_synth(A, col_sorted=1, split_pm1=False)
+        x = np.full(n, m - 1, np.int64)
+        assert np.array_equal(M.spmv_t(tdev(x, dev)).cpu().numpy(), oracle.get().spmv_t(A, x)), n
+        M.close()
+
+
+def test_column_sorted_reordered(dev):
+    check(dev, powerlaw(40_000, 40_000, 32749), 1, col_sorted=1, reorder=True)
