@@ -16,19 +16,12 @@ void SgEncoded::release() {
 namespace {
 
 struct SgPart {  // one group, encoded from offset 0
-  std::vector<uint32_t> ent, choff, cbase;
+  std::vector<uint32_t> ent, cbase;
   std::vector<uint16_t> val;
 };
 
-inline uint32_t sg_tag(uint32_t v, uint32_t m, bool split) {
-  if (!split) return TAG_GEN;
-  if (v == 1) return TAG_PLUS;  // m = 2: 1 = -1 counts as +1
-  if (v == m - 1) return TAG_MINUS;
-  return TAG_GEN;
-}
-
-// rows [r0, r1) of A: entries sorted by (column, row), cut into chunks within 65,536-column panels
-void encode_group(const RCsr& A, int64_t r0, int64_t r1, uint32_t m, bool split, SgPart& P) {
+// rows [r0, r1) of A: entries sorted by (column, row), cut into chunks of columns within 65,536 of their base
+void encode_group(const RCsr& A, int64_t r0, int64_t r1, SgPart& P) {
   const int64_t k0 = A.rp[r0], k1 = A.rp[r1];
   // key: column (bits 30..59) | row in the group (bits 16..29) | value (bits 0..15)
   std::vector<uint64_t> key((size_t)(k1 - k0));
@@ -36,45 +29,34 @@ void encode_group(const RCsr& A, int64_t r0, int64_t r1, uint32_t m, bool split,
     for (int64_t k = A.rp[i]; k < A.rp[i + 1]; ++k)
       key[k - k0] = ((uint64_t)A.col[k] << 30) | ((uint64_t)(i - r0) << SG_ROW_SHIFT) | A.val[k];
   std::sort(key.begin(), key.end());
-  size_t q = 0;
-  uint32_t w[SG_CHUNK];
-  while (q < key.size()) {
-    const uint32_t panel = (uint32_t)(key[q] >> 30) >> 16;
-    size_t q1 = q;
-    while (q1 < key.size() && ((uint32_t)(key[q1] >> 30) >> 16) == panel) ++q1;
-    for (size_t c = q; c < q1; c += SG_CHUNK) {
-      P.choff.push_back((uint32_t)P.val.size());
-      P.cbase.push_back(panel << 16);
-      uint16_t vv[SG_CHUNK];
-      for (int t = 0; t < SG_CHUNK; ++t) {
-        if (c + t < q1) {
-          const uint64_t kk = key[c + t];
-          const uint32_t col = (uint32_t)(kk >> 30), lr = (uint32_t)(kk >> SG_ROW_SHIFT) & (SG_MAX_ROWS - 1);
-          const uint32_t v = (uint32_t)(kk & 0xFFFFu);
-          const uint32_t tag = sg_tag(v, m, split);
-          w[t] = (tag << TAG_SHIFT) | (lr << SG_ROW_SHIFT) | (col & SG_COL_MASK);
-          vv[t] = (uint16_t)v;
-        } else {
-          w[t] = PAD_WORD;
-        }
-      }
-      // entry 64k + l at word 4l + k: one 16-byte load per lane; the general values in the same
-      // lane-major order, so a lane's values are consecutive
-      for (int l = 0; l < 64; ++l)
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t word = w[64 * k + l];
-          P.ent.push_back(word);
-          if ((word >> TAG_SHIFT) == TAG_GEN) P.val.push_back(vv[64 * k + l]);
-        }
+  P.ent.reserve(key.size() + key.size() / 16 + SG_CHUNK);
+  P.val.reserve(P.ent.capacity());
+  for (size_t q = 0; q < key.size();) {
+    const uint32_t base = (uint32_t)(key[q] >> 30);
+    size_t n = 0;  // entries of the chunk
+    while (n < SG_CHUNK && q + n < key.size() && (uint32_t)(key[q + n] >> 30) - base <= SG_COL_MASK) ++n;
+    const size_t at = P.ent.size();
+    P.cbase.push_back(base);
+    P.ent.resize(at + SG_CHUNK);
+    P.val.resize(at + SG_CHUNK);
+    for (size_t t = 0; t < SG_CHUNK; ++t) {
+      const uint64_t kk = key[q + std::min(t, n - 1)];
+      const bool pad = t >= n;
+      const uint32_t col = (uint32_t)(kk >> 30) - base,
+                     row = pad ? (uint32_t)(t % (size_t)(r1 - r0)) & (SG_MAX_ROWS - 1)
+                               : (uint32_t)(kk >> SG_ROW_SHIFT) & (SG_MAX_ROWS - 1);
+      const size_t w = at + 4 * (t % 64) + t / 64;  // entry 64k + l at place 4l + k
+      P.ent[w] = ((pad ? TAG_PAD : 0u) << TAG_SHIFT) | (row << SG_ROW_SHIFT) | col;
+      P.val[w] = pad ? 0 : (uint16_t)(kk & 0xFFFFu);
     }
-    q = q1;
+    q += n;
   }
 }
 
 }  // namespace
 
-void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_groups, bool transposed, int64_t max_col,
-               hipStream_t st, SgEncoded* out) {
+void encode_sg(const RCsr& A, const Modulus& md, int target_groups, bool transposed, int64_t max_col, hipStream_t st,
+               SgEncoded* out) {
   out->release();
   if (!md.small()) fail(FFX_EUNSUPPORTED, "column-sorted groups need m <= 65536");
   const int64_t n = A.nrows, nnz = A.nnz();
@@ -93,17 +75,16 @@ void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_grou
   const int64_t G = (int64_t)ranges.size();
   std::vector<SgPart> parts(G);
 #pragma omp parallel for schedule(dynamic, 1)
-  for (int64_t g = 0; g < G; ++g) encode_group(A, ranges[g].first, ranges[g].second, md.m, split_pm1, parts[g]);
+  for (int64_t g = 0; g < G; ++g) encode_group(A, ranges[g].first, ranges[g].second, parts[g]);
   std::vector<SgGroup> groups(G);
-  size_t nent = 0, nval = 0, nch = 0;
+  size_t nent = 0, nch = 0;
   uint32_t max_rows = 0;
   for (int64_t g = 0; g < G; ++g) {
     groups[g] = SgGroup{(uint32_t)ranges[g].first, (uint32_t)(ranges[g].second - ranges[g].first), (uint32_t)nch,
-                        (uint32_t)parts[g].choff.size()};
+                        (uint32_t)parts[g].cbase.size()};
     max_rows = std::max(max_rows, groups[g].nrows);
     nent += parts[g].ent.size();
-    nval += parts[g].val.size();
-    nch += parts[g].choff.size();
+    nch += parts[g].cbase.size();
   }
   // index of the transposed product: the chunks of each group that hold columns of each panel. Its sums
   // are 32-bit sums of terms below 3m, so the longest column must keep them below 2^32.
@@ -114,13 +95,10 @@ void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_grou
 #pragma omp parallel for schedule(dynamic, 1)
     for (int64_t g = 0; g < G; ++g) {
       const SgPart& Q = parts[g];
-      for (size_t c = 0; c < Q.choff.size(); ++c) {
-        // sorted: entry e of the chunk at word 4*(e % 64) + e / 64; a padded chunk ends before its first PAD
-        const uint32_t* w = &Q.ent[c * SG_CHUNK];
-        int last = SG_CHUNK - 1;
-        while (last > 0 && (w[4 * (last % 64) + last / 64] >> TAG_SHIFT) == TAG_PAD) --last;
+      for (size_t c = 0; c < Q.cbase.size(); ++c) {
+        const uint32_t* w = &Q.ent[c * SG_CHUNK];  // first entry at place 0, last (or padding like it) at the end
         const uint32_t lo = (Q.cbase[c] + (w[0] & SG_COL_MASK)) >> SGT_SHIFT,
-                       hi = (Q.cbase[c] + (w[4 * (last % 64) + last / 64] & SG_COL_MASK)) >> SGT_SHIFT;
+                       hi = (Q.cbase[c] + (w[SG_CHUNK - 1] & SG_COL_MASK)) >> SGT_SHIFT;
         for (uint32_t p = lo; p <= hi; ++p) {
           uint2& r = tindex[(size_t)p * G + g];
           if (r.y == 0) r.x = (uint32_t)c;
@@ -129,24 +107,21 @@ void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_grou
       }
     }
   }
-  if (nent >= UINT32_MAX || nval >= UINT32_MAX) fail(FFX_EUNSUPPORTED, "column-sorted encoding exceeds 2^32 words");
+  if (nent >= UINT32_MAX) fail(FFX_EUNSUPPORTED, "column-sorted encoding exceeds 2^32 words");
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
   const size_t o_g = 0, o_e = o_g + al(G * sizeof(SgGroup)), o_v = o_e + al(nent * 4),
-               o_c = o_v + al(nval * 2 + 16), o_b = o_c + al(nch * 4), o_t = o_b + al(nch * 4),
+               o_b = o_v + al(nent * 2), o_t = o_b + al(nch * 4),
                total = std::max<size_t>(256, o_t + al(tindex.size() * sizeof(uint2)));
   std::vector<unsigned char> host(total, 0);
   std::memcpy(host.data() + o_g, groups.data(), G * sizeof(SgGroup));
-  size_t e = 0, v = 0, c = 0;
+  size_t e = 0, c = 0;
   for (int64_t g = 0; g < G; ++g) {
     const SgPart& P = parts[g];
     std::memcpy(host.data() + o_e + e * 4, P.ent.data(), P.ent.size() * 4);
-    std::memcpy(host.data() + o_v + v * 2, P.val.data(), P.val.size() * 2);
-    uint32_t* ch = (uint32_t*)(host.data() + o_c) + c;
-    for (size_t k = 0; k < P.choff.size(); ++k) ch[k] = P.choff[k] + (uint32_t)v;
+    std::memcpy(host.data() + o_v + e * 2, P.val.data(), P.val.size() * 2);
     std::memcpy(host.data() + o_b + c * 4, P.cbase.data(), P.cbase.size() * 4);
     e += P.ent.size();
-    v += P.val.size();
-    c += P.choff.size();
+    c += P.cbase.size();
   }
   if (!tindex.empty()) std::memcpy(host.data() + o_t, tindex.data(), tindex.size() * sizeof(uint2));
   if (hipMalloc(&out->alloc, total) != hipSuccess)
@@ -161,7 +136,6 @@ void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_grou
   M.groups = (const SgGroup*)(d + o_g);
   M.ent = (const uint32_t*)(d + o_e);
   M.val = (const uint16_t*)(d + o_v);
-  M.choff = (const uint32_t*)(d + o_c);
   M.cbase = (const uint32_t*)(d + o_b);
   M.rowmap = nullptr;
   M.tindex = tindex.empty() ? nullptr : (const uint2*)(d + o_t);
@@ -173,7 +147,7 @@ void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_grou
   M.mu = md.mu;
   out->ngroups = G;
   out->device_bytes = (int64_t)total;
-  out->stream_bytes = (int64_t)(G * sizeof(SgGroup) + nent * 4 + nval * 2 + nch * 8);
+  out->stream_bytes = (int64_t)(G * sizeof(SgGroup) + nent * 6 + nch * 4);
 }
 
 }  // namespace ffx

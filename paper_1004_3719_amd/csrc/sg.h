@@ -13,17 +13,19 @@
 // (Section 2.2) with the reduction taken once per row at the end: for
 // m <= 65536 a term is below 2^32, so no row can overflow 64 bits.
 //
-// Layout. Entry word: tag (2 bits, as in the tiles) | row in the group (14
-// bits) | column - panel base (16 bits). The entries of a group are sorted by
-// column and cut into chunks of 256 words; a chunk never spans two panels of
-// 65,536 columns (the last chunk of a panel is padded), and stores its panel
-// base in `cbase` and the offset of its general values in `choff`. Entry e of
-// a chunk is gathered by lane e mod 64 of the e/64-th gather instruction, so
-// one instruction covers 64 consecutive sorted columns; the chunk stores entry
-// 64k + l at word 4l + k, so lane l reads its four entries with one 16-byte
-// load. General values follow the same lane-major order, so a lane's (at most
-// four) values are consecutive and one 12-byte load fetches them: each chunk
-// costs a lane one entry load, one value load and four gathers.
+// Layout. The entries of a group are sorted by column and cut into chunks of
+// 256. Entry word: tag (2 bits, 0 or TAG_PAD) | row in the group (14 bits) |
+// column - chunk base (16 bits); a chunk stores its base, its first
+// column, and ends where the next column would not fit. Every entry,
+// +-1 or not, has its 16-bit value at the same place of `val`: a term is then
+// one multiplication whatever the entry, where compacted values took four
+// ballots, the selection of a value from the three words loaded and two
+// branches on the tag per entry, which the kernels spent more time on than the
+// 1.2 bytes per entry they saved (60% of +-1). Entry e of a chunk is taken by
+// lane e mod 64 as its e/64-th, so one step covers 64 consecutive sorted
+// columns; the chunk stores entry 64k + l at place 4l + k, so lane l reads its
+// four words with one 16-byte load and its values with one 8-byte load. Padding
+// at a chunk's end has the value 0 and the column of the last entry.
 #pragma once
 
 #include "ffx_impl.h"
@@ -48,9 +50,8 @@ static_assert(sizeof(SgGroup) == 16, "group layout");
 struct SgMat {
   const SgGroup* groups;
   const uint32_t* ent;     // SG_CHUNK words per chunk
-  const uint16_t* val;     // general values, in entry order
-  const uint32_t* choff;   // per chunk: index of its first general value
-  const uint32_t* cbase;   // per chunk: column of its panel's first column
+  const uint16_t* val;     // SG_CHUNK values per chunk
+  const uint32_t* cbase;   // per chunk: the column its entries count from
   const uint32_t* rowmap;  // when not null, row r of the product is written to row rowmap[r] of y
   const uint2* tindex;     // [panel][group]: the chunks (relative to the group) with columns of the panel,
                            // first and one past the last; null when there is no index

@@ -1,6 +1,6 @@
 // The one-vector product on column-sorted row groups (layout in sg.h).
 #include <algorithm>
-#include <mutex>
+#include <type_traits>
 
 #include "launch.h"
 #include "sg.h"
@@ -14,118 +14,119 @@ constexpr int SG_U = 2;           // chunks per wave in flight
 // two on one CU would leave another CU idle).
 constexpr size_t SG_LDS_FLOOR = 96 * 1024;
 
-__device__ inline uint32_t sg_lanes_below(uint64_t mask) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+
+// This lane's four entry words of chunk ch, and their values two to a word (streamed once)
+struct SgLane {
+  uint32_t w[4], p[2];
+  __device__ inline void words(const SgMat& G, uint32_t ch, uint32_t lane) {
+    const u32x4_t q = __builtin_nontemporal_load((const u32x4_t*)(G.ent + (size_t)ch * SG_CHUNK) + lane);
+    w[0] = q.x;
+    w[1] = q.y;
+    w[2] = q.z;
+    w[3] = q.w;
+  }
+  __device__ inline void values(const SgMat& G, uint32_t ch, uint32_t lane) {
+    const u32x2_t q = __builtin_nontemporal_load((const u32x2_t*)(G.val + (size_t)ch * SG_CHUNK) + lane);
+    p[0] = q.x;
+    p[1] = q.y;
+  }
+  __device__ inline uint32_t val(int k) const { return (k & 1) ? p[k / 2] >> 16 : p[k / 2] & 0xFFFFu; }
+  __device__ inline uint32_t col(int k) const { return w[k] & SG_COL_MASK; }
+  __device__ inline uint32_t row(int k) const { return (w[k] >> SG_ROW_SHIFT) & (SG_MAX_ROWS - 1); }
+};
+
+// v*x below 2^32 for residues of at most 16 bits, in one full-rate instruction
+__device__ inline uint32_t sg_mul(uint32_t v, uint32_t x) { return __umul24(v, x); }
+
+template <typename Tv>
+__device__ inline void sg_write(const SgMat& G, const SgGroup& g, const unsigned long long* acc, Tv* y, uint32_t alpha,
+                                uint32_t beta, uint16_t* y16) {
+  for (uint32_t r = threadIdx.x; r < g.nrows; r += SG_THREADS) {
+    const uint32_t row = g.row0 + r, to = G.rowmap ? G.rowmap[row] : row;
+    const uint32_t res = mod_u64(acc[r], G.m, G.mu);
+    const uint32_t out = (alpha == 1 && beta == 0) ? res : axpby(alpha, res, beta, beta ? (uint32_t)y[to] : 0u, G.m, G.mu);
+    y[to] = (Tv)out;
+    if (y16) y16[to] = (uint16_t)out;  // the next product's 16-bit x
+  }
 }
 
-// GF2: a matrix mod 2 times one bit-packed word per row (32 vectors over GF(2)): x and y are words
-// (stride ldx, ldy), a row's sum is the exclusive or of its columns' words (32-bit LDS sums).
-template <typename Tx, typename Tv, int NT, int U, bool GF2>
-__global__ __launch_bounds__(NT) void k_sg(SgMat G, const Tx* __restrict__ x, Tv* __restrict__ y, uint32_t alpha,
-                                           uint32_t beta, uint16_t* __restrict__ y16, int64_t ldx, int64_t ldy) {
+// GF2: a matrix mod 2 times one bit-packed word per row (32 vectors over GF(2)):
+// x and y are words (stride ldx, ldy), a row's sum is the exclusive or of its
+// columns' words (32-bit LDS sums).
+// Bound by the gathers: one costs the vector cache about 86 cycles here (it
+// serves a lane or so per cycle however few lines the lanes share). On the
+// 2,000,000-row power-law matrix a product took 85.6 us when the kernel decoded
+// compacted values, 80.0 with each entry's loaded. Four chunks in flight instead
+// of two: the same. A wave copying the columns its next 256 or 128 entries span
+// to LDS and gathering from there, four windows ahead: 108 us.
+template <typename Tx, typename Tv, int U, bool GF2>
+__global__ __launch_bounds__(SG_THREADS) void k_sg(SgMat G, const Tx* __restrict__ x, Tv* __restrict__ y,
+                                                   uint32_t alpha, uint32_t beta, uint16_t* __restrict__ y16,
+                                                   int64_t ldx, int64_t ldy) {
   extern __shared__ __align__(16) unsigned long long acc[];
   uint32_t* accx = (uint32_t*)acc;  // GF2
-  constexpr uint32_t NW = NT / WAVE;
+  constexpr uint32_t NW = SG_THREADS / WAVE;
   const SgGroup g = G.groups[blockIdx.x];
-  const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
-  for (uint32_t r = tid; r < g.nrows; r += NT) {
+  const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+  for (uint32_t r = tid; r < g.nrows; r += SG_THREADS) {
     if constexpr (GF2) accx[r] = 0u;
     else acc[r] = 0ull;
   }
   __syncthreads();
-  // the entry words of the next U chunks are requested before the values and gathers of the
-  // current ones, so each pass waits on one round trip to memory instead of two
-  uint32_t w[U][4], vo[U], cb[U];
-  auto load_words = [&](uint32_t ch0, uint32_t (&ww)[U][4], uint32_t (&vv)[U], uint32_t (&cc)[U]) {
+  // the entries of the next U chunks are requested before the gathers of the current ones, so each
+  // pass waits on one round trip to memory instead of two
+  SgLane e[U], en[U];
+  uint32_t cb[U], cbn[U];
+  auto load = [&](uint32_t ch0, SgLane (&q)[U], uint32_t (&c)[U]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t ch = ch0 + u * NW;
-      const bool ok = ch < g.nchunks;
-      typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-      const u32x4_t q = ok ? __builtin_nontemporal_load((const u32x4_t*)(G.ent + (size_t)(g.c0 + ch) * SG_CHUNK) + lane)
-                           : (u32x4_t)(PAD_WORD);
-      ww[u][0] = q.x;
-      ww[u][1] = q.y;
-      ww[u][2] = q.z;
-      ww[u][3] = q.w;
-      vv[u] = ok ? G.choff[g.c0 + ch] : 0u;
-      cc[u] = ok ? G.cbase[g.c0 + ch] : 0u;
+      c[u] = 0;
+      if (ch < g.nchunks) {
+        q[u].words(G, g.c0 + ch, lane);
+        if constexpr (!GF2) q[u].values(G, g.c0 + ch, lane);
+        c[u] = G.cbase[g.c0 + ch];
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[u].w[k] = PAD_WORD;
+      }
     }
   };
-  load_words(wave, w, vo, cb);
+  load(wave, e, cb);
   for (uint32_t ch0 = wave; ch0 < g.nchunks; ch0 += NW * U) {
-    uint32_t wn[U][4], von[U], cbn[U];
-    load_words(ch0 + NW * U, wn, von, cbn);
-    // values: a lane's general values are consecutive, after those of the lanes below it (four
-    // ballots give their count), and one 12-byte load brings all of them; then x
-    uint32_t v[U][4], xv[U][4];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      uint32_t idx = vo[u], ng = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const bool gen = (w[u][k] >> TAG_SHIFT) == TAG_GEN;
-        idx += sg_lanes_below(__ballot(gen));
-        ng += gen ? 1u : 0u;
-      }
-      uint32_t q0 = 0, q1 = 0, q2 = 0;
-      if (ng) {
-        typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
-        const u32x3_t q = __builtin_nontemporal_load((const u32x3_t*)((const uint32_t*)G.val + (idx >> 1)));
-        q0 = q.x;
-        q1 = q.y;
-        q2 = q.z;
-      }
-      uint32_t j = idx & 1u;  // position of the lane's first value in the 12 bytes (16-bit units)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t tag = w[u][k] >> TAG_SHIFT;
-        const uint32_t d = j < 2 ? q0 : j < 4 ? q1 : q2;
-        v[u][k] = tag == TAG_GEN ? (d >> ((j & 1u) * 16)) & 0xFFFFu : 0u;
-        j += tag == TAG_GEN ? 1u : 0u;
-        const uint32_t col = cb[u] + (w[u][k] & SG_COL_MASK);
-        xv[u][k] = tag != TAG_PAD ? (uint32_t)(GF2 ? x[(int64_t)col * ldx] : x[col]) : 0u;
-      }
-    }
+    load(ch0 + NW * U, en, cbn);
+    uint32_t xv[U][4];
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const uint32_t tag = w[u][k] >> TAG_SHIFT;
-        if (tag != TAG_PAD) {
-          const uint32_t row = (w[u][k] >> SG_ROW_SHIFT) & (SG_MAX_ROWS - 1);
-          if constexpr (GF2) {  // entries are 1 (with values off, a stored value is odd)
-            atomicXor(&accx[row], (tag != TAG_GEN || (v[u][k] & 1u)) ? xv[u][k] : 0u);
-          } else {
-            // a term is below 2^32: (m-1)^2, x or m - x
-            const uint32_t t = tag == TAG_GEN ? v[u][k] * xv[u][k] : tag == TAG_PLUS ? xv[u][k] : G.m - xv[u][k];
-            atomicAdd(&acc[row], (unsigned long long)t);
-          }
-        }
+        const int64_t col = cb[u] + e[u].col(k);
+        xv[u][k] = (e[u].w[k] >> TAG_SHIFT) != TAG_PAD ? (uint32_t)(GF2 ? x[col * ldx] : x[col]) : 0u;
       }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      vo[u] = von[u];
-      cb[u] = cbn[u];
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) w[u][k] = wn[u][k];
+      for (int k = 0; k < 4; ++k)
+        if ((e[u].w[k] >> TAG_SHIFT) != TAG_PAD) {
+          if constexpr (GF2) atomicXor(&accx[e[u].row(k)], xv[u][k]);  // every entry is 1
+          else atomicAdd(&acc[e[u].row(k)], (unsigned long long)sg_mul(e[u].val(k), xv[u][k]));
+        }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      e[u] = en[u];
+      cb[u] = cbn[u];
     }
   }
   __syncthreads();
   if constexpr (GF2) {
-    for (uint32_t r = tid; r < g.nrows; r += NT) {
+    for (uint32_t r = tid; r < g.nrows; r += SG_THREADS) {
       const uint32_t row = g.row0 + r;
       y[(int64_t)(G.rowmap ? G.rowmap[row] : row) * ldy] = (Tv)accx[r];
     }
-    return;
-  }
-  for (uint32_t r = tid; r < g.nrows; r += NT) {
-    const uint32_t row = g.row0 + r;
-    Tv* yr = y + (G.rowmap ? G.rowmap[row] : row);
-    const uint32_t res = mod_u64(acc[r], G.m, G.mu);
-    const uint32_t out = (alpha == 1 && beta == 0) ? res : axpby(alpha, res, beta, beta ? (uint32_t)*yr : 0u, G.m, G.mu);
-    *yr = (Tv)out;
-    if (y16) y16[G.rowmap ? G.rowmap[row] : row] = (uint16_t)out;  // the next product's 16-bit x
+  } else {
+    sg_write(G, g, acc, y, alpha, beta, y16);
   }
 }
 
@@ -136,36 +137,25 @@ template <typename Tx, typename Tv, bool GF2 = false>
 static hipError_t sg_go(const SgMat& G, const Tx* x, Tv* y, uint32_t alpha, uint32_t beta, uint16_t* y16,
                         hipStream_t st, int64_t ldx = 1, int64_t ldy = 1) {
   const size_t lds = std::max<size_t>((size_t)G.max_rows * 8, SG_LDS_FLOOR);
-  auto k = k_sg<Tx, Tv, SG_THREADS, SG_U, GF2>;
-  // the kernel's LDS limit is raised once per device to the most any group can need (the
-  // attribute is a host call that would otherwise cost a few microseconds per product)
-  static std::mutex mu;
-  static bool done[64] = {};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  auto k = k_sg<Tx, Tv, SG_U, GF2>;
+  hipError_t e = raise_lds_limit((const void*)k, (int)SG_LDS_MAX);
   if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  {
-    std::lock_guard<std::mutex> lock(mu);
-    if (!done[dev]) {
-      e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SG_LDS_MAX);
-      if (e != hipSuccess) return e;
-      done[dev] = true;
-    }
-  }
   hipLaunchKernelGGL(k, dim3(G.ngroups), dim3(SG_THREADS), lds, st, G, x, y, alpha, beta, y16, ldx, ldy);
   return hipGetLastError();
+}
+
+template <typename Tv>
+static hipError_t sg_by_x(const SgMat& G, const void* x, const uint16_t* x16, Tv* y, uint32_t alpha, uint32_t beta,
+                          uint16_t* y16, hipStream_t st) {
+  if (!x16) return sg_go<Tv, Tv>(G, (const Tv*)x, y, alpha, beta, y16, st);
+  return sg_go<uint16_t, Tv>(G, x16, y, alpha, beta, y16, st);
 }
 
 hipError_t launch_sg(const SgMat& G, ffx_dtype dt, const void* x, const uint16_t* x16, void* y, uint32_t alpha,
                      uint32_t beta, hipStream_t st, uint16_t* y16) {
   if (G.ngroups == 0) return hipSuccess;
-  if (dt == FFX_I32) {
-    if (x16) return sg_go<uint16_t, int32_t>(G, x16, (int32_t*)y, alpha, beta, y16, st);
-    return sg_go<int32_t, int32_t>(G, (const int32_t*)x, (int32_t*)y, alpha, beta, y16, st);
-  }
-  if (x16) return sg_go<uint16_t, int64_t>(G, x16, (int64_t*)y, alpha, beta, y16, st);
-  return sg_go<int64_t, int64_t>(G, (const int64_t*)x, (int64_t*)y, alpha, beta, y16, st);
+  if (dt == FFX_I32) return sg_by_x<int32_t>(G, x, x16, (int32_t*)y, alpha, beta, y16, st);
+  return sg_by_x<int64_t>(G, x, x16, (int64_t*)y, alpha, beta, y16, st);
 }
 
 hipError_t launch_sg_gf2(const SgMat& G, const uint32_t* X, int64_t ldx, uint32_t* Y, int64_t ldy, hipStream_t st) {
@@ -186,19 +176,19 @@ hipError_t launch_sg_gf2(const SgMat& G, const uint32_t* X, int64_t ldx, uint32_
 // Groups are dealt out to the parts in turn, since a band puts most of a
 // panel's entries in neighbouring groups. Bound by the latency of a round
 // (stage, then three or four chunks per wave). One vector, 1,000,000 power-law
-// rows (17.2 M entries): 167 us through binned records.
+// rows (17.2 M entries): 167 us through binned records, 86 with compacted values,
+// 75 now.
 constexpr uint32_t SGT_XROWS = 44 * 1024;  // staged 16-bit x entries
 constexpr uint32_t SGT_ROUND = 32;         // groups staged at a time, at most
-constexpr int SGT_U = 2;                   // chunks per wave in flight (four: 77 us against 72 in the kernel)
-constexpr size_t SGT_LDS = ((size_t)4 << SGT_SHIFT) + SGT_XROWS * 2;
+constexpr int SGT_U = 2;                   // chunks per wave in flight (three or four: the same)
+constexpr size_t SGT_LDS = (((size_t)1 << SGT_SHIFT) + WAVE) * 4 + SGT_XROWS * 2;  // the sums and 64 spare ones
 
 __global__ __launch_bounds__(SG_THREADS) void k_sg_t(SgMat G, const uint16_t* __restrict__ x16, uint32_t P, uint32_t Q,
                                                      uint32_t slots, uint32_t slot_rows, uint32_t mu32,
                                                      uint32_t* __restrict__ part) {
   extern __shared__ __align__(16) unsigned long long acc[];
-  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
   uint32_t* sums = (uint32_t*)acc;
-  uint16_t* xs = (uint16_t*)(sums + (1u << SGT_SHIFT));
+  uint16_t* xs = (uint16_t*)(sums + (1u << SGT_SHIFT) + WAVE);
   constexpr uint32_t NW = SG_THREADS / WAVE;
   constexpr int U = SGT_U;
   const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
@@ -225,30 +215,26 @@ __global__ __launch_bounds__(SG_THREADS) void k_sg_t(SgMat G, const uint16_t* __
     }
     const uint32_t total = (uint32_t)__shfl((int)pre, (int)SGT_ROUND - 1);
     pre -= n;  // chunks of the round before this group's
-    // the entry words of the wave's first chunks are requested before x is staged
-    uint32_t w[U][4], vo[U], cb[U], xo[U];
-    auto load_words = [&](uint32_t j) {
+    // the entries of the wave's first chunks are requested before x is staged
+    SgLane e[U];
+    uint32_t cb[U], xo[U];
+    auto load = [&](uint32_t j) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const uint32_t jj = j + u * NW;
-        u32x4_t e = (u32x4_t)(PAD_WORD);
-        vo[u] = cb[u] = xo[u] = 0;
+        cb[u] = xo[u] = 0;
         if (jj < total) {  // the same in the whole wave
           const int k = __builtin_popcountll(__ballot(lane < ng && pre <= jj)) - 1;
           const uint32_t ch = (uint32_t)__builtin_amdgcn_readlane((int)c0, k) + jj -
                               (uint32_t)__builtin_amdgcn_readlane((int)pre, k);
-          e = __builtin_nontemporal_load((const u32x4_t*)(G.ent + (size_t)ch * SG_CHUNK) + lane);
-          vo[u] = G.choff[ch];
-          cb[u] = G.cbase[ch];
+          e[u].words(G, ch, lane);
+          e[u].values(G, ch, lane);
+          cb[u] = G.cbase[ch] - j0;
           xo[u] = (uint32_t)__builtin_amdgcn_readlane((int)xoff, k);
         }
-        w[u][0] = e.x;
-        w[u][1] = e.y;
-        w[u][2] = e.z;
-        w[u][3] = e.w;
       }
     };
-    load_words(wave);
+    load(wave);
     // x of the groups, from the 16-byte boundary before their first row
     const uint32_t per = slot_rows / 8;
     for (uint32_t i = tid; i < ng * per; i += SG_THREADS) {
@@ -259,42 +245,17 @@ __global__ __launch_bounds__(SG_THREADS) void k_sg_t(SgMat G, const uint16_t* __
     }
     __syncthreads();
     for (uint32_t j = wave; j < total; j += NW * U) {
-      if (j != wave) load_words(j);
+      if (j != wave) load(j);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        uint32_t idx = vo[u], ngen = 0;
+        if (j + u * NW >= total) break;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const bool gen = (w[u][k] >> TAG_SHIFT) == TAG_GEN;
-          idx += sg_lanes_below(__ballot(gen));
-          ngen += gen ? 1u : 0u;
-        }
-        uint32_t q0 = 0, q1 = 0, q2 = 0;
-        if (ngen) {
-          typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
-          const u32x3_t v = __builtin_nontemporal_load((const u32x3_t*)((const uint32_t*)G.val + (idx >> 1)));
-          q0 = v.x;
-          q1 = v.y;
-          q2 = v.z;
-        }
-        uint32_t at = idx & 1u;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t tag = w[u][k] >> TAG_SHIFT;
-          const uint32_t d = at < 2 ? q0 : at < 4 ? q1 : q2;
-          const uint32_t v = (d >> ((at & 1u) * 16)) & 0xFFFFu;
-          at += tag == TAG_GEN ? 1u : 0u;
-          const uint32_t col = cb[u] + (w[u][k] & SG_COL_MASK);
-          if (tag == TAG_PAD || (col >> SGT_SHIFT) != p) continue;
-          const uint32_t xv = xs[xo[u] + ((w[u][k] >> SG_ROW_SHIFT) & (SG_MAX_ROWS - 1))];
-          uint32_t t;
-          if (tag == TAG_GEN) {
-            t = v * xv;                       // below 2^32
-            t -= __umulhi(t, mu32) * G.m;     // the quotient is at most two low: below 3m
-          } else {
-            t = tag == TAG_PLUS ? xv : G.m - xv;
-          }
-          atomicAdd(&sums[col & ((1u << SGT_SHIFT) - 1)], t);
+          uint32_t t = sg_mul(e[u].val(k), xs[xo[u] + e[u].row(k)]);  // below 2^32
+          t -= __umul24(__umulhi(t, mu32), G.m);  // the quotient is below 2^16 and at most two low: below 3m
+          // a column of another panel (below j0 it wraps) goes to the spare sums
+          const uint32_t at = min(cb[u] + e[u].col(k), (1u << SGT_SHIFT) + lane);
+          atomicAdd(&sums[at], t);
         }
       }
     }
