@@ -98,9 +98,9 @@ __global__ __launch_bounds__(TILE_THREADS, batch_min_blocks<AR>()) void k_batch(
         else if (kind == TK_LONG) long_tile<AR, Tx, Tv, 1, 2>(A, T, X, ldx, Y, O.ldy, 1, 1, 0, lds);
         else stream_tile_1<AR, Tx, Tv, 2>(A, T, X, ldx, Y, O.ldy, 1, 0, lds);
       } else {
-        if (kind == TK_SELL) sell_tile_rc<AR, Tx, Tv, SC>(A, T, X, ldx, Y, O.ldy, sc, 1, 0);
+        if (kind == TK_SELL) sell_tile_q<AR, Tx, Tv, SC>(A, T, X, ldx, Y, O.ldy, sc, 1, 0);
         else if (kind == TK_LONG) long_tile<AR, Tx, Tv, SC, 1>(A, T, X, ldx, Y, O.ldy, sc, 1, 0, lds);
-        else stream_tile_s<AR, Tx, Tv, SC>(A, T, X, ldx, Y, O.ldy, sc, 1, 0, lds);
+        else stream_tile_b<AR, Tx, Tv, SC>(A, T, X, ldx, Y, O.ldy, sc, 1, 0, lds);
       }
       __syncthreads();  // LDS is reused by the next item
     }
@@ -141,22 +141,23 @@ __global__ void k_batch_reset(uint32_t* counter, int n) {
 }
 
 template <class AR>
-static size_t batch_lds(int64_t mte, int sc) {
-  size_t a = tiles_lds_bytes<AR>(mte, sc);
+static size_t batch_lds(int64_t mtr, int64_t mte, int sc) {  // at most 53 KB (256 rows, 4,096 entries, 8 columns)
+  size_t a = tiles_lds_bytes<AR>(mtr, mte, sc);
   return a < 16 ? 16 : a;
 }
 
 // One class's persistent launch over its items (qinfo: the class's queue table, counter: its NQ counters).
 static hipError_t batch_launch_class(int ak, ffx_dtype dt, bool x16, int cls, const DevMat* mats,
                                      const BatchOperand* ops, const BatchItem* items, const uint32_t* qinfo,
-                                     uint32_t* counter, int grid, int64_t mte, hipStream_t st) {
+                                     uint32_t* counter, int grid, int64_t mtr, int64_t mte,
+                                     hipStream_t st) {
   auto go = [&](auto ar) {
     using AR = decltype(ar);
     auto launch = [&](auto tx, auto tv, auto scv) {
       using Tx = decltype(tx);
       using Tv = decltype(tv);
       constexpr int SC = decltype(scv)::value;
-      hipLaunchKernelGGL((k_batch<AR, Tx, Tv, SC>), dim3(grid), dim3(TILE_THREADS), batch_lds<AR>(mte, SC), st, mats,
+      hipLaunchKernelGGL((k_batch<AR, Tx, Tv, SC>), dim3(grid), dim3(TILE_THREADS), batch_lds<AR>(mtr, mte, SC), st, mats,
                          ops, items, qinfo, counter);
     };
     auto by_dt = [&](auto scv) {
@@ -209,7 +210,7 @@ struct ffx_batch_s {
   std::vector<ffx_matrix> mats;
   std::vector<int32_t> s;
   int ak = 0;
-  int64_t mte = 0;
+  int64_t mtr = 0, mte = 0;  // rows and entries of the largest STREAM tiles
   int ncu = 0;
   ffx_batch_params params{};
   DevMat* d_mats = nullptr;
@@ -351,7 +352,7 @@ static void batch_run(ffx_batch_s* B, const void* const* X, const int64_t* ldx, 
   auto grid_of = [&](int c) { return (int)std::min<int64_t>((int64_t)B->ncu * wpc, B->cls_n[c]); };
   auto launch_class = [&](int c, hipStream_t s) {
     return batch_launch_class(B->ak, dt, x16, c, B->d_mats, B->d_ops, B->d_items + B->cls_first[c],
-                              B->d_qinfo + c * 2 * NQ, B->d_counter + c * NQ, grid_of(c), B->mte, s);
+                              B->d_qinfo + c * 2 * NQ, B->d_counter + c * NQ, grid_of(c), B->mtr, B->mte, s);
   };
   auto launch_x16 = [&](hipStream_t s) -> hipError_t {
     if (!x16) return hipSuccess;
@@ -497,6 +498,7 @@ ffx_status ffx_batch_create(int32_t count, const ffx_matrix* mats, const int32_t
           fail(FFX_EINVAL, "matrix %d: all matrices of a batch need the same modulus and accumulator", k);
         dm[k] = mats[k]->A.dm;
         B->mte = std::max(B->mte, mats[k]->A.max_tile_entries);
+        B->mtr = std::max<int64_t>(B->mtr, mats[k]->A.dm.max_tile_rows);
         sig << "|" << mats[k]->info.nrows << "x" << mats[k]->info.nnz << "s" << s[k];
       }
       B->signature = sig.str();

@@ -120,9 +120,9 @@ __global__ __launch_bounds__(TILE_THREADS) void k_seq_step_gf2(DevMat A, Gf2SeqA
   int32_t* Y = (int32_t*)(last ? q.Wlast : q.W[(i + 1) & 1]);
   const Tile T = A.tiles[blockIdx.x];
   switch (tile_kind(T.kind)) {
-    case TK_SELL: sell_tile_rc<ArGF2, int32_t, int32_t, S>(A, T, X, w, Y, w, w, 1, 0); break;
+    case TK_SELL: sell_tile_q<ArGF2, int32_t, int32_t, S>(A, T, X, w, Y, w, w, 1, 0); break;
     case TK_LONG: long_tile<ArGF2, int32_t, int32_t, S, 1>(A, T, X, w, Y, w, w, 1, 0, lds); break;
-    default: stream_tile_s<ArGF2, int32_t, int32_t, S>(A, T, X, w, Y, w, w, 1, 0, lds);
+    default: stream_tile_b<ArGF2, int32_t, int32_t, S>(A, T, X, w, Y, w, w, 1, 0, lds);
   }
   if (last) return;  // W_L only
   // the projection reads back only rows this workgroup wrote: a workgroup barrier orders them
@@ -160,7 +160,7 @@ hipError_t launch_sequence_gf2(const DevMat& A, int64_t mte, int w, const uint32
   q.L = L;
   q.w = w;
   const int S_ = w <= 2 ? 2 : w <= 4 ? 4 : w <= 8 ? 8 : 16;  // the multi-vector tiles, as for residues
-  size_t lds = tiles_lds_bytes<ArGF2>(mte, S_);
+  size_t lds = tiles_lds_bytes<ArGF2>(A.max_tile_rows, mte, S_);
   const size_t plds = gf2_projection_lds(w);
   if (lds < plds) lds = plds;
   hipLaunchKernelGGL(k_seq_first_gf2, dim3(A.ntiles), dim3(TILE_THREADS), plds, st, A, q);

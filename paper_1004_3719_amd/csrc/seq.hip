@@ -442,7 +442,7 @@ __device__ __forceinline__ void seq_step(const DevMat& A, const SeqArgs& q, int3
       return;
     }
     if (tile_kind(T.kind) == TK_LONG) long_tile<AR, Tw, Tw, S, 1>(A, T, Win, ldin, Wout, s, s, 1, 0, lds);
-    else stream_tile_s<AR, Tw, Tw, S>(A, T, Win, ldin, Wout, s, s, 1, 0, lds);
+    else stream_tile_b<AR, Tw, Tw, S>(A, T, Win, ldin, Wout, s, s, 1, 0, lds);
     if (last) return;  // W_L only: no partials needed
     // the projection reads back only rows this workgroup wrote: a workgroup barrier orders them
     __syncthreads();
@@ -484,12 +484,17 @@ template <class AR, typename Ts, bool ONLY_SELL>
 static hipError_t seq_go(const DevMat& A, int64_t mte, const SeqArgs& q, int batch, hipStream_t user) {
   const int s = q.s;
   const int S = s <= 2 ? 2 : s <= 4 ? 4 : s <= 8 ? 8 : 16;  // the step always runs the multi-vector tiles
-  size_t lds = tiles_lds_bytes<AR>(mte, S);
+  size_t lds = tiles_lds_bytes<AR>(A.max_tile_rows, mte, S);
   if (lds < SELL_SLICES * TILE_THREADS * sizeof(uint64_t)) lds = SELL_SLICES * TILE_THREADS * sizeof(uint64_t);
   // s = 8: half-row lanes (sell_slice_h8), whose LDS holds 4 waves x 2 KB of rows and the 256 sums
   const bool h8 = s == 8;
   const size_t h8_lds = 4 * 512 * sizeof(uint32_t) + TILE_THREADS * sizeof(uint64_t);
   if (h8 && lds < h8_lds) lds = h8_lds;
+  if (lds > 64 * 1024) {  // s > 8 on STREAM tiles of 4,096 entries and 256 rows
+    hipError_t e = raise_lds_limit((const void*)k_seq_step<AR, Ts, 16, ONLY_SELL>,
+                                   (int)tiles_lds_bytes<AR>(TILE_THREADS, 4096, 16));
+    if (e != hipSuccess) return e;
+  }
   int64_t* base = const_cast<int64_t*>(q.base);
   auto step = [&](hipStream_t st, int32_t j) {
     dim3 g((h8 ? A.ntiles * 2 : A.ntiles * SELL_SLICES) + NMID + 1), b(TILE_THREADS);

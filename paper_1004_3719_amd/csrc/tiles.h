@@ -7,7 +7,8 @@
 //           gathered x) go to LDS and each row is summed from LDS by a group
 //           of lanes sized to the tile (the CSR-Stream scheme of Greathouse
 //           and Daga, SC'14, designed for AMD GPUs); for s > 1 vectors the
-//           chunk stages words and values in LDS and each lane sums one row.
+//           chunk stages words and values in LDS and the lanes take equal runs
+//           of entries.
 //   LONG    one row too long for a STREAM tile: all 256 lanes sweep it and
 //           the partial sums meet through shuffles and LDS.
 //   SELL    up to 4 slices of 64 rows stored column-major (ELL on a GPU is
@@ -33,6 +34,7 @@
 #include <algorithm>
 
 #include "ffx_impl.h"
+#include "launch.h"
 
 namespace ffx {
 
@@ -182,6 +184,14 @@ __device__ inline typename AR::Prod term(uint32_t tag, uint32_t v, uint32_t x, u
   if (tag == TAG_PLUS) return lift<AR>(x, m);
   if (tag == TAG_MINUS) return lift<AR>(m - x, m);
   return (typename AR::Prod)0;
+}
+
+// The value of an entry word, +-1 as 1 and m - 1 and 0 for padding: with several
+// vectors a term is then one product without a branch on the tag (whose lanes
+// differ), and the words of an entry are looked at once, not per vector.
+__device__ inline uint32_t entry_value(uint32_t w, uint32_t v, uint32_t m) {
+  const uint32_t tag = w >> TAG_SHIFT;
+  return tag == TAG_GEN ? v : tag == TAG_PLUS ? 1u : tag == TAG_MINUS ? m - 1 : 0u;
 }
 
 // S accumulators of one lane with a shared countdown to the next reduction.
@@ -399,6 +409,104 @@ struct Chunk4 {
   }
 };
 
+// The components of a row of X that one lane gathers: 16 bytes, so a row of
+// eight int32 is two lanes. (Two loads of one row by the same lane, for four
+// int64, are two requests to the L2: 72 us against 58 on 300,000 rows, s = 3.)
+template <typename Tx, int S>
+constexpr int lane_comps() { return sizeof(Tx) == 8 ? (S >= 2 ? 2 : 1) : S >= 4 ? 4 : S; }
+
+// A lane's piece of rows: C components from c0 on, of which [lo, hi) are the
+// lane's own. The last piece of a row ends where the row ends and then overlaps
+// the one before it, so that every piece is one wide load without a condition;
+// a lane with no component of its own (lo >= hi) loads that piece too. Only
+// rows shorter than a piece are loaded element by element (SHORT: s = C - 1,
+// three vectors of four, or one where a step always takes two); the tile code
+// is built for either, since a choice at every gather makes the compiler split
+// the wide loads into what the choices have in common (8 vectors of 32 bits on
+// the 1M power law: 356 us with such a choice, 207 without).
+template <int C>
+struct RowPiece {
+  int c0, lo, hi;
+  __device__ inline RowPiece(uint32_t piece, int s) {
+    c0 = max(0, min((int)piece * C, s - C));
+    lo = (int)piece * C - c0;
+    hi = min(C, s - c0);
+  }
+  __device__ inline bool used() const { return lo < hi; }
+};
+
+// Where lane slots (C to a piece) hold component c of a row of s.
+template <int C>
+__device__ inline int piece_slot(int c, int s) {
+  const int p = c / C * C;
+  return p + c - max(0, min(p, s - C));
+}
+
+typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));  // an element's alignment is enough
+typedef uint32_t u32x4a8 __attribute__((ext_vector_type(4), aligned(8)));  // for a wide load or store
+typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
+
+// The piece's residues of the row of X whose first element is at p. There is no
+// condition on the entry: padding gathers row 0 with the value 0.
+template <bool SHORT, typename Tx, int C>
+__device__ inline void gather_comps(const Tx* p, const RowPiece<C>& rp, uint32_t* out) {
+  if constexpr (SHORT) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) out[c] = c + 1 < C ? (uint32_t)p[c] : 0u;
+    return;
+  }
+  p += rp.c0;
+  if constexpr (sizeof(Tx) == 4 && C == 4) {
+    const u32x4a4 q = *(const u32x4a4*)p;
+    out[0] = q.x, out[1] = q.y, out[2] = q.z, out[3] = q.w;
+  } else if constexpr (sizeof(Tx) == 4 && C == 2) {
+    const u32x2a4 q = *(const u32x2a4*)p;
+    out[0] = q.x, out[1] = q.y;
+  } else if constexpr (sizeof(Tx) == 8 && C == 2) {  // residues: the low words
+    const u32x4a8 q = *(const u32x4a8*)p;
+    out[0] = q.x, out[1] = q.z;
+  } else {
+#pragma unroll
+    for (int c = 0; c < C; ++c) out[c] = (uint32_t)p[c];
+  }
+}
+
+// The piece of row `row` of Y from the residues r.
+template <typename Tv, int C>
+__device__ inline void write_comps(const DevMat& A, Tv* Y, int64_t ldy, uint32_t row, const RowPiece<C>& rp, uint32_t* r,
+                                   uint32_t alpha, uint32_t beta) {
+  if (!rp.used()) return;
+  Tv* y = Y + (int64_t)(A.rowmap ? A.rowmap[row] : row) * ldy;
+  if (alpha != 1 || beta != 0) {
+    uint32_t yo[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) yo[c] = 0u;
+    if (beta) {
+      if (rp.hi == C) gather_comps<false, Tv, C>(y, rp, yo);
+      else gather_comps<true, Tv, C>(y, rp, yo);
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) r[c] = axpby(alpha, r[c], beta, yo[c], A.m, A.mu);
+  }
+  y += rp.c0;
+  if constexpr (C >= 2) {
+    if (rp.lo == 0 && rp.hi == C) {
+      if constexpr (sizeof(Tv) == 4 && C == 4) {
+        *(u32x4a4*)y = (u32x4a4){r[0], r[1], r[2], r[3]};
+      } else if constexpr (sizeof(Tv) == 4) {
+        *(u32x2a4*)y = (u32x2a4){r[0], r[1]};
+      } else {
+#pragma unroll
+        for (int c = 0; c < C; c += 2) *(u32x4a8*)(y + c) = (u32x4a8){r[c], 0u, r[c + 1], 0u};
+      }
+      return;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    if (c >= rp.lo && c < rp.hi) y[c] = (Tv)r[c];
+}
+
 // ------------------------------- SELL tile ---------------------------------
 // A slice stores its rows in groups of 4 columns: group g is 256 words, word
 // 4*lane + k being entry 4g + k of the slice's row `lane`; swidth holds the
@@ -446,106 +554,139 @@ __device__ inline void sell_tile(const DevMat& A, const Tile& T, const Tx* __res
   write_row<Tv, S>(A, Y, ldy, row, r, s, alpha, beta);
 }
 
-// SELL with s > 1 vectors: lane (r, c) of a pass handles component c of row
-// r, so the S lanes of one row gather one contiguous piece of X (one cache
-// line for s = 8 int64) instead of S separate lookups per lane. The entry
-// words and values of each row are loaded once per 4-column group with lane =
-// row and broadcast to the pass lanes with shuffles.
-template <class AR, typename Tx, typename Tv, int S>
-__device__ inline void sell_tile_rc(const DevMat& A, const Tile& T, const Tx* __restrict__ X, int64_t ldx,
-                                    Tv* __restrict__ Y, int64_t ldy, int s, uint32_t alpha, uint32_t beta) {
-  constexpr int RPW = WAVE / S;                       // rows per pass; S passes cover the slice
-  constexpr int KB = S >= 16 ? 1 : S >= 8 ? 2 : WIDE;  // group columns per batch: 16 gathers in flight
+// SELL with s > 1 vectors: CL = S / C lanes share a row, each with C of its
+// components, so a pass covers 64 / CL rows and a gather is one 16-byte load per
+// lane (a vector-cache lane costs about a cycle whatever its width: with a lane
+// per component a row of eight cost eight). The entry words and values of each
+// row are loaded once per 4-column group with lane = row and handed to the
+// lanes of its pass by shuffles. 300,000 rows of 20 entries, m = 65521: 102 ->
+// 49 us with 8 vectors, 230 -> 69 with 16, unchanged (44, 43) with 4, where a
+// lane held the whole row before too. Bound by the gathers: 64-byte rows at 8.
+template <class AR, typename Tx, typename Tv, int S, bool SHORT>
+__device__ inline void sell_tile_m(const DevMat& A, const Tile& T, const Tx* __restrict__ X, int64_t ldx,
+                                   Tv* __restrict__ Y, int64_t ldy, int s, uint32_t alpha, uint32_t beta) {
+  constexpr int C = lane_comps<Tx, S>(), CL = S / C, RPP = WAVE / CL;
+  constexpr int KB = CL >= 4 ? 1 : CL == 2 ? 2 : WIDE;  // group columns per batch
+  constexpr int DB = CL >= 4 ? 1 : 4 / CL;                   // diagonals per batch
   const uint32_t lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
   const uint32_t nsl = T.ne;
   if (wave >= nsl) return;
   uint32_t off = 0;
   for (uint32_t k = 0; k < wave; ++k) off += A.swidth[T.aux + k];
   const uint32_t groups = A.swidth[T.aux + wave];
-  const uint32_t comp = lane % S, sub = lane / S;
-  const bool cok = (int)comp < s;
+  const uint32_t sub = lane / CL;
+  const RowPiece<C> piece(lane % CL, s);
   const uint32_t* ent = A.ent + T.e0 + (size_t)off * SELL_GROUP + lane * WIDE;
   const uint32_t* choff = A.choff + T.c0 + off;
-  uint32_t prow[S];  // row of each pass
+  uint32_t prow[CL];  // row of each pass
 #pragma unroll
-  for (int p = 0; p < S; ++p) {
-    uint32_t slot = wave * WAVE + p * RPW + sub;
+  for (int p = 0; p < CL; ++p) {
+    const uint32_t slot = wave * WAVE + p * RPP + sub;
     prow[p] = (T.kind & TF_SORTED) ? A.perm[T.row0 + slot] : T.row0 + slot;
   }
-  LaneAcc<AR, S> acc;  // acc.a[p]: pass p
+  LaneAcc<AR, CL * C> acc;  // acc.a[p * C + c]: component c0 + c of pass p
   acc.init(A);
   // band part
   const uint32_t nd = tile_nd(T.kind), rows_in_tile = tile_rows(T.kind);
-  for (uint32_t d = 0; d < nd; ++d) {
-    const int32_t o = A.boffs[T.boff + d];
+  for (uint32_t d0 = 0; d0 < nd; d0 += DB) {
+    uint32_t v[DB][CL], xv[DB][CL][C];
 #pragma unroll
-    for (int p = 0; p < S; ++p) {
-      uint32_t slot = wave * WAVE + p * RPW + sub;
-      int64_t col = (int64_t)prow[p] + o;
-      bool ok = prow[p] < A.nrows && col >= 0 && col < (int64_t)A.ncols && cok;
-      uint32_t v = ok ? ldval<typename AR::ValT>(A.bval, T.b0 + d * rows_in_tile + slot) : 0u;
-      uint32_t x = ok ? (uint32_t)X[col * ldx + comp] : 0u;
-      acc.a[p] += mul_term<AR>(v, x, A.m);
-    }
-    acc.tick(A);
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+      for (int p = 0; p < CL; ++p) {
+        const uint32_t slot = wave * WAVE + p * RPP + sub;
+        const int64_t col = d0 + d < nd ? (int64_t)prow[p] + A.boffs[T.boff + d0 + d] : -1;
+        const bool ok = prow[p] < A.nrows && col >= 0 && col < (int64_t)A.ncols;
+        v[d][p] = ok ? ldval<typename AR::ValT>(A.bval, T.b0 + (d0 + d) * rows_in_tile + slot) : 0u;
+        gather_comps<SHORT, Tx, C>(X + (ok ? col : 0) * ldx, piece, xv[d][p]);
+      }
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+      if (d0 + d < nd) {
+#pragma unroll
+        for (int p = 0; p < CL; ++p)
+#pragma unroll
+          for (int c = 0; c < C; ++c) acc.a[p * C + c] += mul_term<AR>(v[d][p], xv[d][p][c], A.m);
+        acc.tick(A);
+      }
   }
+  u32x4 next = groups ? __builtin_nontemporal_load((const u32x4*)ent) : (u32x4)(PAD_WORD);
   for (uint32_t g = 0; g < groups; ++g) {
-    uint32_t w[WIDE], v[WIDE];
-    {
-      u32x4 q = __builtin_nontemporal_load((const u32x4*)(ent + (size_t)g * SELL_GROUP));
-      w[0] = q.x;
-      w[1] = q.y;
-      w[2] = q.z;
-      w[3] = q.w;
-    }
+    const uint32_t w[WIDE] = {next.x, next.y, next.z, next.w};
+    uint32_t v[WIDE];
     load_values4<AR>(A, w, choff[g], v);
 #pragma unroll
+    for (int k = 0; k < WIDE; ++k) v[k] = entry_value(w[k], v[k], A.m);
+    // the next group's words are requested before this one's gathers
+    if (g + 1 < groups) next = __builtin_nontemporal_load((const u32x4*)(ent + (size_t)(g + 1) * SELL_GROUP));
+    // (with two or more batches a real loop: unrolled, the next batch's shuffles and gathers are hoisted
+    // over this one's terms, which cost 156 registers at S = 16 against 100)
+#pragma unroll 1
     for (int k0 = 0; k0 < WIDE; k0 += KB) {
+      uint32_t wk[KB], vk[KB];
+#pragma unroll
+      for (int k = 0; k < KB; ++k) {
+        wk[k] = KB == WIDE ? w[k] : KB == 2 ? (k0 ? w[2 + k] : w[k]) : k0 < 2 ? (k0 ? w[1] : w[0]) : k0 == 2 ? w[2] : w[3];
+        vk[k] = KB == WIDE ? v[k] : KB == 2 ? (k0 ? v[2 + k] : v[k]) : k0 < 2 ? (k0 ? v[1] : v[0]) : k0 == 2 ? v[2] : v[3];
+      }
       // every gather of the batch is issued before the first term is added
-      uint32_t xv[KB][S];
+      uint32_t xv[KB][CL][C];
 #pragma unroll
       for (int k = 0; k < KB; ++k)
 #pragma unroll
-        for (int p = 0; p < S; ++p) {
-          uint32_t wp = (uint32_t)__shfl((int)w[k0 + k], p * RPW + (int)sub);
-          xv[k][p] = ((wp >> TAG_SHIFT) != TAG_PAD && cok) ? (uint32_t)X[(int64_t)(wp & COL_MASK) * ldx + comp] : 0u;
+        for (int p = 0; p < CL; ++p) {
+          const uint32_t wp = CL == 1 ? wk[k] : (uint32_t)__shfl((int)wk[k], p * RPP + (int)sub);
+          gather_comps<SHORT, Tx, C>(X + (int64_t)(wp & COL_MASK) * ldx, piece, xv[k][p]);
         }
 #pragma unroll
       for (int k = 0; k < KB; ++k) {
 #pragma unroll
-        for (int p = 0; p < S; ++p) {
-          int src = p * RPW + (int)sub;
-          uint32_t wp = (uint32_t)__shfl((int)w[k0 + k], src), vp = (uint32_t)__shfl((int)v[k0 + k], src);
-          acc.a[p] += term<AR>(wp >> TAG_SHIFT, vp, xv[k][p], A.m);
+        for (int p = 0; p < CL; ++p) {
+          const uint32_t vp = CL == 1 ? vk[k] : (uint32_t)__shfl((int)vk[k], p * RPP + (int)sub);
+#pragma unroll
+          for (int c = 0; c < C; ++c) acc.a[p * C + c] += mul_term<AR>(vp, xv[k][p][c], A.m);
         }
         acc.tick(A);
       }
     }
   }
 #pragma unroll
-  for (int p = 0; p < S; ++p) {
-    if (prow[p] < A.nrows && cok) {
-      uint32_t r = AR::reduce(acc.a[p], A);
-      Tv* yr = Y + (int64_t)(A.rowmap ? A.rowmap[prow[p]] : prow[p]) * ldy + comp;
-      uint32_t yo = beta ? (uint32_t)*yr : 0u;
-      *yr = (Tv)((alpha == 1 && beta == 0) ? r : axpby(alpha, r, beta, yo, A.m, A.mu));
+  for (int p = 0; p < CL; ++p)
+    if (prow[p] < A.nrows) {
+      uint32_t r[C];
+#pragma unroll
+      for (int c = 0; c < C; ++c) r[c] = AR::reduce(acc.a[p * C + c], A);
+      write_comps<Tv, C>(A, Y, ldy, prow[p], piece, r, alpha, beta);
     }
-  }
+}
+
+template <class AR, typename Tx, typename Tv, int S>
+__device__ inline void sell_tile_q(const DevMat& A, const Tile& T, const Tx* __restrict__ X, int64_t ldx,
+                                   Tv* __restrict__ Y, int64_t ldy, int s, uint32_t alpha, uint32_t beta) {
+  constexpr int C = lane_comps<Tx, S>();
+  if constexpr (S <= C)  // fewer vectors than a piece holds: only here
+    if (s < C) return sell_tile_m<AR, Tx, Tv, S, true>(A, T, X, ldx, Y, ldy, s, alpha, beta);
+  sell_tile_m<AR, Tx, Tv, S, false>(A, T, X, ldx, Y, ldy, s, alpha, beta);
 }
 
 // ------------------------------- LONG tile ---------------------------------
-template <class AR, typename Tx, typename Tv, int S, int U>
-__device__ inline void long_tile(const DevMat& A, const Tile& T, const Tx* __restrict__ X, int64_t ldx,
+// Every wave sweeps every fourth chunk of the row, CL lanes to an entry as in
+// sell_tile_q (one vector: a lane to an entry); the lanes' sums of a component
+// meet through shuffles, the waves' in LDS.
+template <class AR, typename Tx, typename Tv, int S, int U, bool SHORT>
+__device__ inline void long_tile_m(const DevMat& A, const Tile& T, const Tx* __restrict__ X, int64_t ldx,
                                  Tv* __restrict__ Y, int64_t ldy, int s, uint32_t alpha, uint32_t beta,
                                  unsigned char* lds) {
   using Acc = typename AR::Acc;
   constexpr uint32_t NW = TILE_THREADS / WAVE;
+  constexpr int C = lane_comps<Tx, S>(), CL = S / C, EPP = WAVE / CL;
   const uint32_t lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
   const uint32_t nchunks = (T.ne + WCHUNK - 1) / WCHUNK;
-  LaneAcc<AR, S> acc;
+  const uint32_t sub = lane / CL;
+  const RowPiece<C> piece(lane % CL, s);
+  LaneAcc<AR, C> acc;
   acc.init(A);
-  band_terms<AR, Tx, S>(A, T, acc, T.row0, 0, 1, threadIdx.x, TILE_THREADS, X, ldx, s);
-  auto words = [&](Chunk4<AR, Tx, S, U>& b, uint32_t ch0) {
+  auto words = [&](auto& b, uint32_t ch0) {
     b.load_words(
         [&](int u) -> const u32x4* {
           uint32_t ch = ch0 + u * NW, k = ch * WCHUNK + lane * WIDE;
@@ -556,31 +697,76 @@ __device__ inline void long_tile(const DevMat& A, const Tile& T, const Tx* __res
           return ch < nchunks ? A.choff[T.c0 + ch] : 0u;
         });
   };
-  for (uint32_t ch0 = wave; ch0 < nchunks; ch0 += NW * U) {
-    Chunk4<AR, Tx, S, U> b;
-    words(b, ch0);
-    b.load_gathers(A, X, ldx, s);
-    b.accumulate(A, acc, s);
+  if constexpr (S == 1) {
+    band_terms<AR, Tx, 1>(A, T, acc, T.row0, 0, 1, threadIdx.x, TILE_THREADS, X, ldx, s);
+    for (uint32_t ch0 = wave; ch0 < nchunks; ch0 += NW * U) {
+      Chunk4<AR, Tx, 1, U> b;
+      words(b, ch0);
+      b.load_gathers(A, X, ldx, s);
+      b.accumulate(A, acc, s);
+    }
+  } else {
+    const uint32_t nd = tile_nd(T.kind);
+    for (uint32_t d = threadIdx.x / CL; d < nd; d += TILE_THREADS / CL) {
+      const int64_t col = (int64_t)T.row0 + A.boffs[T.boff + d];
+      const bool ok = col >= 0 && col < (int64_t)A.ncols;
+      const uint32_t v = ok ? ldval<typename AR::ValT>(A.bval, T.b0 + d) : 0u;
+      uint32_t xv[C];
+      gather_comps<SHORT, Tx, C>(X + (ok ? col : 0) * ldx, piece, xv);
+#pragma unroll
+      for (int c = 0; c < C; ++c) acc.a[c] += mul_term<AR>(v, xv[c], A.m);
+      acc.tick(A);
+    }
+    for (uint32_t ch = wave; ch < nchunks; ch += NW) {
+      Chunk4<AR, Tx, 1, 1> b;
+      words(b, ch);
+      load_values4<AR>(A, b.w[0], b.vo[0], b.v[0]);
+#pragma unroll
+      for (int k = 0; k < WIDE; ++k) b.v[0][k] = entry_value(b.w[0][k], b.v[0][k], A.m);
+      for (int p = 0; p < CL; ++p) {  // entries 4*(p * EPP + sub) + k of the chunk
+        uint32_t w[WIDE], xv[WIDE][C];
+        const int src = p * EPP + (int)sub;
+#pragma unroll
+        for (int k = 0; k < WIDE; ++k) {
+          w[k] = CL == 1 ? b.w[0][k] : (uint32_t)__shfl((int)b.w[0][k], src);
+          gather_comps<SHORT, Tx, C>(X + (int64_t)(w[k] & COL_MASK) * ldx, piece, xv[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < WIDE; ++k) {
+          const uint32_t v = CL == 1 ? b.v[0][k] : (uint32_t)__shfl((int)b.v[0][k], src);
+          if ((w[k] >> TAG_SHIFT) == TAG_PAD) continue;
+#pragma unroll
+          for (int c = 0; c < C; ++c) acc.a[c] += mul_term<AR>(v, xv[k][c], A.m);
+          acc.tick(A);
+        }
+      }
+    }
   }
   acc.to_residues(A);
   Acc* red = (Acc*)lds;  // [4 waves][S]
 #pragma unroll
-  for (int c = 0; c < S; ++c) {
+  for (int c = 0; c < C; ++c) {
     Acc v = acc.a[c];
-    for (int o = WAVE / 2; o > 0; o >>= 1) v += shfl_xor_acc(v, o, WAVE);
-    if (lane == 0) red[wave * S + c] = v;
+    for (int o = WAVE / 2; o >= CL; o >>= 1) v += shfl_xor_acc(v, o, WAVE);
+    if (lane < (uint32_t)CL) red[wave * S + lane * C + c] = v;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t r[S];
-#pragma unroll
-    for (int c = 0; c < S; ++c) {
-      Acc t = 0;
-      for (uint32_t q = 0; q < NW; ++q) t += red[q * S + c];
-      r[c] = AR::reduce(t, A);
-    }
-    write_row<Tv, S>(A, Y, ldy, T.row0, r, s, alpha, beta);
+  if (threadIdx.x < (uint32_t)S && (int)threadIdx.x < s) {
+    Acc t = 0;
+    for (uint32_t q = 0; q < NW; ++q) t += red[q * S + piece_slot<C>(threadIdx.x, s)];
+    uint32_t r = AR::reduce(t, A);
+    write_comps<Tv, 1>(A, Y, ldy, T.row0, RowPiece<1>(threadIdx.x, s), &r, alpha, beta);
   }
+}
+
+template <class AR, typename Tx, typename Tv, int S, int U>
+__device__ inline void long_tile(const DevMat& A, const Tile& T, const Tx* __restrict__ X, int64_t ldx,
+                                 Tv* __restrict__ Y, int64_t ldy, int s, uint32_t alpha, uint32_t beta,
+                                 unsigned char* lds) {
+  constexpr int C = lane_comps<Tx, S>();
+  if constexpr (S > 1 && S <= C)
+    if (s < C) return long_tile_m<AR, Tx, Tv, S, U, true>(A, T, X, ldx, Y, ldy, s, alpha, beta, lds);
+  long_tile_m<AR, Tx, Tv, S, U, false>(A, T, X, ldx, Y, ldy, s, alpha, beta, lds);
 }
 
 // ------------------------------- STREAM tile -------------------------------
@@ -677,260 +863,142 @@ __device__ inline void stream_tile_1(const DevMat& A, const Tile& T, const Tx* _
   }
 }
 
-// s > 1 vectors on a tile whose rows are skewed (TF_LONGROWS): a row of up to
-// STREAM_LONG_ROW entries is summed by its own lane, a longer one by the whole
-// workgroup, lane = (slot, component), so a power-law row inside a tile does
-// not serialize on one lane. The workgroup's partial sums of a long row meet
-// through shuffles and LDS atomics.
-
-// LDS of stream_tile_s for a tile of ne entries (see the layout there).
+// LDS of stream_tile_b for tiles of at most nr rows and ne entries.
 template <class AR, int S>
-__host__ __device__ inline size_t stream_s_lds_bytes(int64_t ne) {
-  const size_t maxl = (size_t)ne / (STREAM_LONG_ROW + 1) + 1;
-  return (size_t)ne * 8 + 16 + 4 + maxl * 4 + 16 + maxl * S * sizeof(typename AR::Acc);  // with alignment slack
+__host__ __device__ inline size_t stream_b_lds_bytes(int64_t nr, int64_t ne) {
+  return (size_t)nr * S * sizeof(typename AR::Acc) + (size_t)(nr + 4) / 4 * 16 + (size_t)(ne + 3) / 4 * 32;
 }
 
-template <class AR, typename Tx, typename Tv, int S>
-__device__ inline void stream_tile_s_long(const DevMat& A, const Tile& T, const Tx* __restrict__ X, int64_t ldx,
+// s > 1 vectors: words and values are staged in LDS, then each group of S / C
+// lanes (C components to a lane) takes an equal run of consecutive entries, adds
+// up the terms of a row in registers and adds them to the row's sums in LDS
+// where the row ends. A tile's time then depends on its entries alone: with a
+// lane per row and a kernel of its own for tiles with rows above 64 entries, the
+// power-law matrix (1,000,000 rows, s = 8) took 481 us, its longest lanes
+// walking 64 entries while most were done after three; now 207 us (17.2 M
+// gathers of 32 bytes from all over a 32 MB X: 2.7 TB/s of them, L2 misses).
+template <class AR, typename Tx, typename Tv, int S, bool SHORT>
+__device__ inline void stream_tile_m(const DevMat& A, const Tile& T, const Tx* __restrict__ X, int64_t ldx,
                                      Tv* __restrict__ Y, int64_t ldy, int s, uint32_t alpha, uint32_t beta,
                                      unsigned char* lds) {
   using Acc = typename AR::Acc;
   constexpr uint32_t NW = TILE_THREADS / WAVE;
-  constexpr int U = 2;
-  // LDS: words [ne], values [ne], long-row count, long rows [maxl], their sums [maxl][S]
-  uint32_t* sw = (uint32_t*)lds;
-  uint32_t* sv = sw + T.ne;
-  const uint32_t maxl = T.ne / (STREAM_LONG_ROW + 1) + 1;
-  uint32_t* lcount = (uint32_t*)(((uintptr_t)(sv + T.ne) + 15) & ~(uintptr_t)15);
-  uint32_t* lrows = lcount + 1;
-  Acc* lacc = (Acc*)(((uintptr_t)(lrows + maxl) + 15) & ~(uintptr_t)15);
+  constexpr int C = lane_comps<Tx, S>(), CL = S / C;
+  constexpr uint32_t NG = TILE_THREADS / CL;
+  constexpr int EU = C >= 4 || sizeof(Tx) == 8 ? 4 : 8;  // entries of a run whose gathers are in flight together
   const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
-  const uint32_t nchunks = (T.ne + WCHUNK - 1) / WCHUNK;
-  const uint32_t nr = tile_rows(T.kind);
-  if (tid == 0) *lcount = 0;
-  uint32_t kb = 0, ke = 0;
-  if (tid < nr) {
-    kb = A.rowp[T.aux + tid] - T.e0;
-    ke = A.rowp[T.aux + tid + 1] - T.e0;
-  }
-  for (uint32_t ch0 = wave; ch0 < nchunks; ch0 += NW * U) {
-    uint32_t w[U][WIDE], vo[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      uint32_t ch = ch0 + u * NW, k = ch * WCHUNK + lane * WIDE;
-      u32x4 q = (ch < nchunks && k < T.ne) ? __builtin_nontemporal_load((const u32x4*)(A.ent + T.e0 + k))
-                                           : (u32x4)(PAD_WORD);
-      w[u][0] = q.x;
-      w[u][1] = q.y;
-      w[u][2] = q.z;
-      w[u][3] = q.w;
-      vo[u] = ch < nchunks ? A.choff[T.c0 + ch] : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      uint32_t v[WIDE];
-      load_values4<AR>(A, w[u], vo[u], v);
-#pragma unroll
-      for (int k = 0; k < WIDE; ++k) {
-        uint32_t e = (ch0 + u * NW) * WCHUNK + lane * WIDE + k;
-        if (e < T.ne) {
-          sw[e] = w[u][k];
-          sv[e] = v[k];
-        }
-      }
+  const uint32_t ne = T.ne, nr = tile_rows(T.kind);
+  const uint32_t nchunks = (ne + WCHUNK - 1) / WCHUNK;
+  Acc* rowsum = (Acc*)lds;                          // [nr][S]
+  uint32_t* rps = (uint32_t*)(rowsum + nr * S);     // [nr + 1] tile-relative row starts
+  u32x4* sw = (u32x4*)(rps + (nr + 4) / 4 * 4);     // [ne] words, in fours
+  u32x4* sv = sw + (ne + 3) / 4;                    // [ne] values
+  const uint32_t grp = tid / CL, slot = tid % CL * C;
+  const RowPiece<C> piece(tid % CL, s);
+  for (uint32_t ch = wave; ch < nchunks; ch += NW) {
+    const uint32_t k = ch * WCHUNK + lane * WIDE;
+    const u32x4 q = k < ne ? __builtin_nontemporal_load((const u32x4*)(A.ent + T.e0 + k)) : (u32x4)(PAD_WORD);
+    const uint32_t w[WIDE] = {q.x, q.y, q.z, q.w};
+    uint32_t v[WIDE];
+    load_values4<AR>(A, w, A.choff[T.c0 + ch], v);
+    if (k < ne) {
+      sw[k / WIDE] = q;
+      sv[k / WIDE] = (u32x4){entry_value(w[0], v[0], A.m), entry_value(w[1], v[1], A.m), entry_value(w[2], v[2], A.m),
+                             entry_value(w[3], v[3], A.m)};
     }
   }
-  __syncthreads();
-  const bool mine = tid < nr;
-  const bool islong = mine && ke - kb > STREAM_LONG_ROW;
-  uint32_t lidx = 0;
-  if (islong) {
-    lidx = atomicAdd(lcount, 1u);
-    lrows[lidx] = tid;
-  }
-  const uint32_t row = T.row0 + tid;
-  if (mine) {
-    LaneAcc<AR, S> acc;
+  if (tid < nr) rps[tid] = A.rowp[T.aux + tid] - T.e0;
+  if (tid == 0) rps[nr] = ne;  // nr may be 256: the sentinel needs its own writer
+  // the rows' sums start from their band parts
+  const uint32_t nd = tile_nd(T.kind);
+  for (uint32_t r = grp; r < nr; r += NG) {
+    LaneAcc<AR, C> acc;
     acc.init(A);
-    band_terms<AR, Tx, S>(A, T, acc, row, tid, nr, 0, 1, X, ldx, s);
-    if (islong) {  // a long row's sums start from its band part, as residues; the workgroup adds the rest
-      acc.to_residues(A);
+    constexpr int DB = 4;
+    for (uint32_t d0 = 0; d0 < nd; d0 += DB) {
+      uint32_t v[DB], xv[DB][C];
 #pragma unroll
-      for (int c = 0; c < S; ++c) lacc[lidx * S + c] = acc.a[c];
-    } else {
-      // EU entries of the row at a time: their gathers are all issued before the
-      // first term is added (16 in flight per lane)
-      constexpr int EU = S >= 16 ? 1 : 16 / S;
-      for (uint32_t k0 = kb; k0 < ke; k0 += EU) {
-        uint32_t w[EU], xv[EU][S];
+      for (int d = 0; d < DB; ++d) {
+        const bool in = d0 + d < nd;
+        const int64_t col = in ? (int64_t)(T.row0 + r) + A.boffs[T.boff + d0 + d] : -1;
+        const bool ok = col >= 0 && col < (int64_t)A.ncols;
+        v[d] = ok ? ldval<typename AR::ValT>(A.bval, T.b0 + (d0 + d) * nr + r) : 0u;
+        gather_comps<SHORT, Tx, C>(X + (ok ? col : 0) * ldx, piece, xv[d]);
+      }
 #pragma unroll
-        for (int e = 0; e < EU; ++e) {
-          w[e] = k0 + e < ke ? sw[k0 + e] : PAD_WORD;
-          const Tx* xr = X + (int64_t)(w[e] & COL_MASK) * ldx;
-          const bool live = (w[e] >> TAG_SHIFT) != TAG_PAD;
+      for (int d = 0; d < DB; ++d)
+        if (d0 + d < nd) {
 #pragma unroll
-          for (int c = 0; c < S; ++c) xv[e][c] = (live && c < s) ? (uint32_t)xr[c] : 0u;
-        }
-#pragma unroll
-        for (int e = 0; e < EU; ++e) {
-          const uint32_t tag = w[e] >> TAG_SHIFT, v = k0 + e < ke ? sv[k0 + e] : 0u;
-#pragma unroll
-          for (int c = 0; c < S; ++c)
-            if (c < s) acc.a[c] += term<AR>(tag, v, xv[e][c], A.m);
+          for (int c = 0; c < C; ++c) acc.a[c] += mul_term<AR>(v[d], xv[d][c], A.m);
           acc.tick(A);
         }
-      }
-      uint32_t r[S];
-#pragma unroll
-      for (int c = 0; c < S; ++c) r[c] = AR::reduce(acc.a[c], A);
-      write_row<Tv, S>(A, Y, ldy, row, r, s, alpha, beta);
     }
+    acc.to_residues(A);
+#pragma unroll
+    for (int c = 0; c < C; ++c) rowsum[r * S + slot + c] = acc.a[c];
   }
-  __syncthreads();  // the long-row list and the band sums of long rows are complete
-  const uint32_t nl = *lcount;
-  if (nl) {
-    constexpr uint32_t SLOTS = TILE_THREADS / S;
-    constexpr int EU2 = 4;
-    const uint32_t comp = tid % S, slot = tid / S;
-    const bool cok = (int)comp < s;
-    for (uint32_t q = 0; q < nl; ++q) {
-      const uint32_t r = lrows[q];
-      const uint32_t b = A.rowp[T.aux + r] - T.e0, e = A.rowp[T.aux + r + 1] - T.e0;
-      LaneAcc<AR, 1> pa;
-      pa.init(A);
-      for (uint32_t k0 = b + slot; k0 < e; k0 += SLOTS * EU2) {
-        uint32_t w[EU2], xv[EU2];
+  __syncthreads();
+  const uint32_t per = ((ne + NG - 1) / NG + WIDE - 1) / WIDE * WIDE;
+  const uint32_t p0 = grp * per, p1 = min(ne, p0 + per);
+  if (p0 < p1 && piece.used()) {
+    uint32_t lo = 0, hi = nr;  // last row r with rps[r] <= p0
+    while (hi - lo > 1) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (rps[mid] <= p0) lo = mid;
+      else hi = mid;
+    }
+    uint32_t r = lo, next = rps[r + 1];
+    LaneAcc<AR, C> acc;
+    acc.init(A);
+    auto flush = [&] {
+      acc.to_residues(A);
 #pragma unroll
-        for (int u = 0; u < EU2; ++u) {
-          const uint32_t k = k0 + u * SLOTS;
-          w[u] = k < e ? sw[k] : PAD_WORD;
-          xv[u] = ((w[u] >> TAG_SHIFT) != TAG_PAD && cok) ? (uint32_t)X[(int64_t)(w[u] & COL_MASK) * ldx + comp] : 0u;
-        }
+      for (int c = 0; c < C; ++c) atomicAdd(&rowsum[r * S + slot + c], acc.a[c]);
+    };
+    for (uint32_t p = p0; p < p1; p += EU) {
+      uint32_t w[EU], v[EU], xv[EU][C];
 #pragma unroll
-        for (int u = 0; u < EU2; ++u) {
-          const uint32_t k = k0 + u * SLOTS;
-          pa.a[0] += term<AR>(w[u] >> TAG_SHIFT, k < e ? sv[k] : 0u, xv[u], A.m);
-          pa.tick(A);
-        }
+      for (int e = 0; e < EU; e += WIDE) {
+        const bool in = p + e < p1;
+        const u32x4 q = in ? sw[(p + e) / WIDE] : (u32x4)(PAD_WORD), z = in ? sv[(p + e) / WIDE] : (u32x4)(0u);
+        w[e] = q.x, w[e + 1] = q.y, w[e + 2] = q.z, w[e + 3] = q.w;
+        v[e] = z.x, v[e + 1] = z.y, v[e + 2] = z.z, v[e + 3] = z.w;
       }
-      pa.to_residues(A);
-      Acc t = pa.a[0];
-      for (int o = S; o < WAVE; o <<= 1) t += shfl_xor_acc(t, o, WAVE);  // the wave's slots of one component
-      if (lane < (uint32_t)S && cok) atomicAdd(&lacc[q * S + comp], t);
-    }
-    __syncthreads();
-    if (islong) {
-      uint32_t r[S];
 #pragma unroll
-      for (int c = 0; c < S; ++c) r[c] = AR::reduce(lacc[lidx * S + c], A);
-      write_row<Tv, S>(A, Y, ldy, row, r, s, alpha, beta);
+      for (int e = 0; e < EU; ++e) gather_comps<SHORT, Tx, C>(X + (int64_t)(w[e] & COL_MASK) * ldx, piece, xv[e]);
+#pragma unroll
+      for (int e = 0; e < EU; ++e) {
+        if (p + e >= p1) break;
+        while (p + e >= next) {
+          flush();
+          acc.init(A);
+          next = rps[++r + 1];
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc.a[c] += mul_term<AR>(v[e], xv[e][c], A.m);
+        acc.tick(A);
+      }
     }
+    flush();
+  }
+  __syncthreads();
+  for (uint32_t i = tid; i < nr * S; i += TILE_THREADS) {
+    const uint32_t r = i / S, c = i % S;
+    if ((int)c >= s) continue;
+    const uint32_t row = T.row0 + r, res = AR::reduce(rowsum[r * S + piece_slot<C>(c, s)], A);
+    Tv* y = Y + (int64_t)(A.rowmap ? A.rowmap[row] : row) * ldy + c;
+    *y = (Tv)((alpha == 1 && beta == 0) ? res : axpby(alpha, res, beta, beta ? (uint32_t)*y : 0u, A.m, A.mu));
   }
 }
 
-// s > 1 vectors: stage words and values in LDS, one lane per row (correct
-// for every tile; tiles flagged TF_LONGROWS are faster with stream_tile_s_long)
 template <class AR, typename Tx, typename Tv, int S>
-__device__ inline void stream_tile_s(const DevMat& A, const Tile& T, const Tx* __restrict__ X, int64_t ldx,
+__device__ inline void stream_tile_b(const DevMat& A, const Tile& T, const Tx* __restrict__ X, int64_t ldx,
                                      Tv* __restrict__ Y, int64_t ldy, int s, uint32_t alpha, uint32_t beta,
                                      unsigned char* lds) {
-  constexpr uint32_t NW = TILE_THREADS / WAVE;
-  constexpr int U = 2;
-  uint32_t* sw = (uint32_t*)lds;
-  uint32_t* sv = sw + T.ne;
-  const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
-  const uint32_t nchunks = (T.ne + WCHUNK - 1) / WCHUNK;
-  const uint32_t nr = tile_rows(T.kind);
-  uint32_t kb = 0, ke = 0;
-  if (tid < nr) {
-    kb = A.rowp[T.aux + tid] - T.e0;
-    ke = A.rowp[T.aux + tid + 1] - T.e0;
-  }
-  for (uint32_t ch0 = wave; ch0 < nchunks; ch0 += NW * U) {
-    uint32_t w[U][WIDE], vo[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      uint32_t ch = ch0 + u * NW, k = ch * WCHUNK + lane * WIDE;
-      u32x4 q = (ch < nchunks && k < T.ne) ? __builtin_nontemporal_load((const u32x4*)(A.ent + T.e0 + k))
-                                           : (u32x4)(PAD_WORD);
-      w[u][0] = q.x;
-      w[u][1] = q.y;
-      w[u][2] = q.z;
-      w[u][3] = q.w;
-      vo[u] = ch < nchunks ? A.choff[T.c0 + ch] : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      uint32_t idx = vo[u];
-#pragma unroll
-      for (int k = 0; k < WIDE; ++k) idx += lanes_below(__ballot((w[u][k] >> TAG_SHIFT) == TAG_GEN));
-#pragma unroll
-      for (int k = 0; k < WIDE; ++k) {
-        bool gen = (w[u][k] >> TAG_SHIFT) == TAG_GEN;
-        uint32_t v = gen ? ldval<typename AR::ValT>(A.val, idx) : 0u;
-        idx += gen ? 1u : 0u;
-        uint32_t e = (ch0 + u * NW) * WCHUNK + lane * WIDE + k;
-        if (e < T.ne) {
-          sw[e] = w[u][k];
-          sv[e] = v;
-        }
-      }
-    }
-  }
-  __syncthreads();
-  if (tid >= nr) return;
-  const uint32_t row = T.row0 + tid;
-  LaneAcc<AR, S> acc;
-  acc.init(A);
-  band_terms<AR, Tx, S>(A, T, acc, row, tid, nr, 0, 1, X, ldx, s);
-  // EU entries of the row at a time: their gathers are all issued before the
-  // first term is added (16 in flight per lane)
-  constexpr int EU = S >= 16 ? 1 : 16 / S;
-  // s = S with 16-byte aligned rows of X: a row is gathered in 16-byte loads
-  // (two for s = 8 int32 instead of eight 4-byte ones), so the vector cache
-  // looks up each line once per load, not once per component
-  constexpr bool VT = sizeof(Tx) == 4 || sizeof(Tx) == 8;  // int32 or int64 rows (not a 16-bit copy)
-  constexpr int NV = VT && (S * sizeof(Tx)) % 16 == 0 ? (int)((S * sizeof(Tx)) / 16) : 0;
-  const bool vx = NV > 0 && s == S && ((uintptr_t)X & 15) == 0 && ((ldx * (int64_t)sizeof(Tx)) & 15) == 0;
-  for (uint32_t k0 = kb; k0 < ke; k0 += EU) {
-    uint32_t w[EU], xv[EU][S];
-#pragma unroll
-    for (int e = 0; e < EU; ++e) {
-      w[e] = k0 + e < ke ? sw[k0 + e] : PAD_WORD;
-      const Tx* xr = X + (int64_t)(w[e] & COL_MASK) * ldx;
-      const bool live = (w[e] >> TAG_SHIFT) != TAG_PAD;
-      if (NV > 0 && vx) {
-#pragma unroll
-        for (int j = 0; j < (NV > 0 ? NV : 1); ++j) {
-          const u32x4 q = live ? ((const u32x4*)xr)[j] : (u32x4){0u, 0u, 0u, 0u};
-          if constexpr (sizeof(Tx) == 4) {
-            xv[e][4 * j] = q.x;
-            xv[e][4 * j + 1] = q.y;
-            xv[e][4 * j + 2] = q.z;
-            xv[e][4 * j + 3] = q.w;
-          } else if constexpr (sizeof(Tx) == 8) {  // residues: the low words of two int64
-            xv[e][2 * j] = q.x;
-            xv[e][2 * j + 1] = q.z;
-          }
-        }
-      } else {
-#pragma unroll
-        for (int c = 0; c < S; ++c) xv[e][c] = (live && c < s) ? (uint32_t)xr[c] : 0u;
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < EU; ++e) {
-      const uint32_t tag = w[e] >> TAG_SHIFT, v = k0 + e < ke ? sv[k0 + e] : 0u;
-#pragma unroll
-      for (int c = 0; c < S; ++c)
-        if (c < s) acc.a[c] += term<AR>(tag, v, xv[e][c], A.m);
-      acc.tick(A);
-    }
-  }
-  uint32_t r[S];
-#pragma unroll
-  for (int c = 0; c < S; ++c) r[c] = AR::reduce(acc.a[c], A);
-  write_row<Tv, S>(A, Y, ldy, row, r, s, alpha, beta);
+  constexpr int C = lane_comps<Tx, S>();
+  if constexpr (S <= C)  // fewer vectors than a piece holds: only here
+    if (s < C) return stream_tile_m<AR, Tx, Tv, S, true>(A, T, X, ldx, Y, ldy, s, alpha, beta, lds);
+  stream_tile_m<AR, Tx, Tv, S, false>(A, T, X, ldx, Y, ldy, s, alpha, beta, lds);
 }
 
 // ------------------------------- the launch --------------------------------
@@ -944,24 +1012,13 @@ __global__ __launch_bounds__(TILE_THREADS) void k_tiles(DevMat A, const Tx* __re
   switch (tile_kind(T.kind)) {
     case TK_SELL:
       if constexpr (S == 1) sell_tile<AR, Tx, Tv, 1, 4>(A, T, X, ldx, Y, ldy, s, alpha, beta);
-      else sell_tile_rc<AR, Tx, Tv, S>(A, T, X, ldx, Y, ldy, s, alpha, beta);
+      else sell_tile_q<AR, Tx, Tv, S>(A, T, X, ldx, Y, ldy, s, alpha, beta);
       break;
     case TK_LONG: long_tile<AR, Tx, Tv, S, (S == 1 ? U : 1)>(A, T, X, ldx, Y, ldy, s, alpha, beta, lds); break;
     default:
       if constexpr (S == 1) stream_tile_1<AR, Tx, Tv, U>(A, T, X, ldx, Y, ldy, alpha, beta, lds);
-      else if (!(T.kind & TF_LONGROWS)) stream_tile_s<AR, Tx, Tv, S>(A, T, X, ldx, Y, ldy, s, alpha, beta, lds);
-      // (flagged tiles, s > 1: k_tiles_long)
+      else stream_tile_b<AR, Tx, Tv, S>(A, T, X, ldx, Y, ldy, s, alpha, beta, lds);
   }
-}
-
-// The STREAM tiles flagged TF_LONGROWS, for s > 1 (one workgroup each).
-template <class AR, typename Tx, typename Tv, int S>
-__global__ __launch_bounds__(TILE_THREADS) void k_tiles_long(DevMat A, const Tx* __restrict__ X, int64_t ldx,
-                                                             Tv* __restrict__ Y, int64_t ldy, int s, uint32_t alpha,
-                                                             uint32_t beta) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  const Tile T = A.tiles[A.ltiles[blockIdx.x]];
-  stream_tile_s_long<AR, Tx, Tv, S>(A, T, X, ldx, Y, ldy, s, alpha, beta, lds);
 }
 
 template <typename Tv>
@@ -1001,15 +1058,16 @@ __global__ void k_to_u16_x8(const Tv* __restrict__ x, uint16_t* __restrict__ out
   }
 }
 
-// Dynamic LDS of one launch.
+// Dynamic LDS of one launch over tiles of which the STREAM ones have at most
+// max_tile_rows rows and max_tile_entries entries.
 template <class AR>
-inline size_t tiles_lds_bytes(int64_t max_tile_entries, int S) {
+inline size_t tiles_lds_bytes(int64_t max_tile_rows, int64_t max_tile_entries, int S) {
   size_t stream = S == 1 ? TILE_THREADS * sizeof(typename AR::Acc) + (TILE_THREADS + 4) * 4 +
                                (size_t)max_tile_entries * sizeof(typename AR::Prod)
-                  : S == 2  ? stream_s_lds_bytes<AR, 2>(max_tile_entries)
-                  : S == 4  ? stream_s_lds_bytes<AR, 4>(max_tile_entries)
-                  : S == 8  ? stream_s_lds_bytes<AR, 8>(max_tile_entries)
-                            : stream_s_lds_bytes<AR, 16>(max_tile_entries);
+                  : S == 2  ? stream_b_lds_bytes<AR, 2>(max_tile_rows, max_tile_entries)
+                  : S == 4  ? stream_b_lds_bytes<AR, 4>(max_tile_rows, max_tile_entries)
+                  : S == 8  ? stream_b_lds_bytes<AR, 8>(max_tile_rows, max_tile_entries)
+                            : stream_b_lds_bytes<AR, 16>(max_tile_rows, max_tile_entries);
   size_t red = (size_t)(TILE_THREADS / WAVE) * S * sizeof(typename AR::Acc);
   size_t b = stream > red ? stream : red;
   return b < 16 ? 16 : b;
@@ -1028,6 +1086,18 @@ static void launch_s1(const DevMat& A, dim3 grid, size_t lds, const Tx* x, int64
                      beta);
 }
 
+// The most dynamic LDS of a multi-vector launch: 256 rows and 4,096 entries of 16 vectors.
+template <class AR, typename Tv>
+hipError_t raise_tiles_lds(int S) {
+  const int most = (int)tiles_lds_bytes<AR>(TILE_THREADS, 4096, S);
+  switch (S) {
+    case 2: return raise_lds_limit((const void*)k_tiles<AR, Tv, Tv, 2, 4>, most);
+    case 4: return raise_lds_limit((const void*)k_tiles<AR, Tv, Tv, 4, 4>, most);
+    case 8: return raise_lds_limit((const void*)k_tiles<AR, Tv, Tv, 8, 4>, most);
+    default: return raise_lds_limit((const void*)k_tiles<AR, Tv, Tv, 16, 4>, most);
+  }
+}
+
 // x16: when not null, a 16-bit copy of the one vector (s must be 1)
 template <class AR, typename Tv>
 hipError_t launch_tiles_t(const DevMat& A, int64_t max_tile_entries, const void* X, int64_t ldx, void* Y, int64_t ldy,
@@ -1035,7 +1105,11 @@ hipError_t launch_tiles_t(const DevMat& A, int64_t max_tile_entries, const void*
                           uint32_t nblocks = 0) {
   if (A.ntiles == 0) return hipSuccess;
   const int S = s <= 1 ? 1 : s <= 2 ? 2 : s <= 4 ? 4 : s <= 8 ? 8 : 16;
-  size_t lds = tiles_lds_bytes<AR>(max_tile_entries, S);
+  size_t lds = tiles_lds_bytes<AR>(A.max_tile_rows, max_tile_entries, S);
+  if (lds > 64 * 1024) {
+    hipError_t e = raise_tiles_lds<AR, Tv>(S);
+    if (e != hipSuccess) return e;
+  }
   dim3 grid(nblocks ? nblocks : A.ntiles), block(TILE_THREADS);
   const Tv* x = (const Tv*)X;
   Tv* y = (Tv*)Y;
@@ -1057,15 +1131,6 @@ hipError_t launch_tiles_t(const DevMat& A, int64_t max_tile_entries, const void*
     case 4: hipLaunchKernelGGL((k_tiles<AR, Tv, Tv, 4, 4>), grid, block, lds, st, A, x, ldx, y, ldy, s, alpha, beta); break;
     case 8: hipLaunchKernelGGL((k_tiles<AR, Tv, Tv, 8, 4>), grid, block, lds, st, A, x, ldx, y, ldy, s, alpha, beta); break;
     default: hipLaunchKernelGGL((k_tiles<AR, Tv, Tv, 16, 4>), grid, block, lds, st, A, x, ldx, y, ldy, s, alpha, beta); break;
-  }
-  if (A.nltiles && !nblocks) {  // the flagged tiles the launch above left out
-    dim3 lg(A.nltiles);
-    switch (S) {
-      case 2: hipLaunchKernelGGL((k_tiles_long<AR, Tv, Tv, 2>), lg, block, lds, st, A, x, ldx, y, ldy, s, alpha, beta); break;
-      case 4: hipLaunchKernelGGL((k_tiles_long<AR, Tv, Tv, 4>), lg, block, lds, st, A, x, ldx, y, ldy, s, alpha, beta); break;
-      case 8: hipLaunchKernelGGL((k_tiles_long<AR, Tv, Tv, 8>), lg, block, lds, st, A, x, ldx, y, ldy, s, alpha, beta); break;
-      default: hipLaunchKernelGGL((k_tiles_long<AR, Tv, Tv, 16>), lg, block, lds, st, A, x, ldx, y, ldy, s, alpha, beta); break;
-    }
   }
   return hipGetLastError();
 }

@@ -1,0 +1,80 @@
+"""Products with several vectors at the edges of the lanes' pieces of rows:
+widths about a piece (four 32-bit components, two of 64 bits), leading
+dimensions that leave the wide loads at an element's alignment, tiles of the
+most rows and of the most entries, rows over many runs and over many tiles, and
+values at the ends of their range; bit for bit against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+M31 = 2**31 - 1
+FORMATS = ["STREAM", "SELL", "SELL_SORTED", "BAND_STREAM", "BAND_SELL_SORTED"]
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def check(dev, A, s, dtype, ldx_extra, ldy_extra, off, top=False, **opts):
+    from paper_1004_3719_amd import Matrix
+    M = Matrix.from_synth(A, **opts)
+    X = np.full((A.ncols, s), A.m - 1, np.int64) if top else synth.vector(81, 1, A.ncols * s, 0, A.m - 1).reshape(
+        A.ncols, s)
+    Y0 = synth.vector(81, 2, A.nrows * s, 0, A.m - 1).reshape(A.nrows, s)
+
+    def place(v, extra):  # rows of s + extra elements, the first `off` elements into the buffer
+        n, ld = v.shape[0], s + extra
+        flat = torch.full((n * ld + off + 4,), A.m - 1, dtype=dtype, device=dev)
+        t = flat[off:off + n * ld].view(n, ld)[:, :s]
+        t.copy_(torch.from_numpy(v).to(dtype).to(dev))
+        return t, flat
+
+    Xd, _ = place(X, ldx_extra)
+    Yd, flat = place(Y0, ldy_extra)
+    before = flat.clone()
+    M.spmm(Xd, alpha=A.m - 2, beta=A.m // 3, Y=Yd)
+    assert np.array_equal(Yd.cpu().numpy(), oracle.get().spmm(A, X, A.m - 2, A.m // 3, Y0))
+    Yd.copy_(torch.from_numpy(Y0).to(dtype).to(dev))
+    assert torch.equal(flat, before)  # nothing beside the s components was written
+    M.spmm(Xd, Y=Yd)
+    assert np.array_equal(Yd.cpu().numpy(), oracle.get().spmm(A, X))
+    M.close()
+
+
+def mixed(nrows, ncols, m, seed, lmax=3000, val=2**40):
+    A = synth.rows(synth.spec(nrows, ncols, seed, len_kind=synth.LEN_ZIPF, len_a=1, len_b=min(lmax, ncols),
+                              len_alpha=1.6, col_kind=synth.COL_UNIFORM, band_lo=-2, band_hi=2, p_pm1=0.5, val_lo=-val,
+                              val_hi=val))
+    A.m = m
+    return A
+
+
+@pytest.mark.parametrize("m,dtype", [(65521, torch.int32), (M31, torch.int32), (M31, torch.int64)])
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("s", [2, 3, 4, 5, 6, 7, 8, 9, 11, 12, 15, 16])
+def test_pieces(dev, s, fmt, m, dtype):
+    A = mixed(1500, 1501, m, 31 + s)
+    check(dev, A, s, dtype, s % 3, (s + 1) % 4, s % 2 + 1, fixed_format=fmt, tile_entries=256 if s % 2 else 1024)
+
+
+@pytest.mark.parametrize("acc", ["int64", "fp64", "fp32"])
+@pytest.mark.parametrize("s,m,tile_entries", [(2, 2039, 4096), (4, 2039, 256), (16, 2039, 4096)])
+def test_largest_tiles(dev, acc, s, m, tile_entries):
+    # 256 short rows to a tile, then rows of several tiles each, every term the largest
+    n = 1100
+    lens = np.where(np.arange(n) < 900, 4, 0)
+    lens[950], lens[1000], lens[1001] = 4097, 9000, 1
+    rowptr = np.concatenate([[0], np.cumsum(lens)])
+    rng = np.random.default_rng(5)
+    col = rng.integers(0, 9500, rowptr[-1])
+    A = synth.Csr(n, 9500, rowptr.astype(np.int64), col.astype(np.int32), np.full(rowptr[-1], m - 1, np.int64))
+    A.m = m
+    check(dev, A, s, torch.int32, 0, 0, 0, top=True, fixed_format="STREAM", tile_entries=tile_entries, acc=acc)
