@@ -7,7 +7,7 @@
 // PM-Basis splits the order in two halves: the basis M1 of the first half, the
 // middle product R = [x^s1 .. x^(s-1)] (M1 G), the basis M2 of R with M1's
 // degrees, and M = M2 M1. Orders up to LEAF are done by the one-order-at-a-time
-// M-Basis in a single workgroup whose basis lives in LDS. Because M-Basis only
+// M-Basis in one launch, a column of the basis to a workgroup, in LDS. Because M-Basis only
 // looks at the residual coefficient [x^k](M G) and the degrees, the
 // divide-and-conquer result is the same basis, step for step, as M-Basis run
 // over the whole order.
@@ -30,7 +30,7 @@
 
 namespace ffx {
 
-constexpr int SB_LEAF = 32;    // orders done by the in-LDS M-Basis
+constexpr int SB_LEAF = 32;    // orders done by one launch of the in-LDS M-Basis
 constexpr int SB_MAXM = 16;    // rows of the basis
 constexpr int SB_MAXN = 8;     // columns of the series
 constexpr int PM_TILE = 256;   // coefficients per workgroup in the products
@@ -282,224 +282,252 @@ __global__ void __launch_bounds__(PMS_NT) k_polymul_small(const uint32_t* __rest
 }
 
 // One-order-at-a-time basis (M-Basis) of the m x n series G to order sg <= SB_LEAF
-// with shifted degrees d (in/out, device). M: m x m entries of sm >= sg + 1 coefficients.
-// LEAF_NT lanes: the residual takes 8 lanes per entry and the basis update 4 lanes per entry, each
-// over a share of the inner index or of the coefficients.
+// with shifted degrees d_in, written to d_out by workgroup 0 (another buffer: the
+// others may start when it has ended). M: m x m entries of sm >= sg + 1 coefficients.
+//
+// One order is a chain of at most n pivot steps that nothing else can hide, so
+// the rest of the work is taken off that chain. Workgroup c holds column c of M
+// and all of the residual series R = x^-k M G, and carries out the same row
+// operations as the others, so the workgroups need nothing from one another. In
+// a workgroup, waves 0 to 3 (one to a SIMD) eliminate order k: lane & 15 is a
+// row, in the order in which rows become pivots, of two columns of the residual
+// coefficient, the same in each wave, and of one of the 16 columns of the
+// transformation T_k, so that a step is a few moves between lanes and three
+// registers, without LDS or a barrier. The other twelve
+// waves apply T_(k-1) to R and M meanwhile, and one barrier per order hands T_k
+// over; the next residual coefficient is T_k times one coefficient of R.
+//
+// 31 orders of 16 x 8 at p = 2^31 - 1: 363 us as one workgroup that formed each
+// residual from M and G and eliminated behind a barrier per pivot, 85 us now (of
+// 2.6 us per order the pivot steps are 1.3, the update as much: all four SIMDs are
+// busy with multiplications, each a quarter of the rate of an addition).
 constexpr int LEAF_NT = 1024;
+constexpr int LEAF_EW = 4;                                // waves of the elimination
+constexpr int LEAF_AW = LEAF_NT / WAVE - LEAF_EW;         // waves of the update, four rows each
+constexpr int LEAF_RJ = SB_MAXM * SB_MAXN + SB_MAXN;      // words from a coefficient of R to the next, [q][c] each
+constexpr int LEAF_MJ = SB_MAXM + 1;                      // of M's column, [q] each
+constexpr int LEAF_TD = SB_MAXN;                          // a row of T: its entries in the pivots' columns, then
+constexpr int LEAF_TR = SB_MAXN + 4;                      // its diagonal entry (it has no others); to the next row
+static_assert(SB_MAXM == 16 && SB_MAXN == 8 && LEAF_AW % 4 == 0, "lanes of the leaf");
+
+// x mod p, x any sum of two products of residues (or four for p = 2^31 - 1)
+template <bool MERS>
+__device__ inline uint32_t fred(uint64_t x, const Field& F) {
+  if (!MERS) return mod_u64(x, F.p, F.mu);
+  x = (x & 0x7FFFFFFFull) + (x >> 31);  // below 2^34
+  x = (x & 0x7FFFFFFFull) + (x >> 31);  // below p + 9
+  return (uint32_t)(x >= 0x7FFFFFFFull ? x - 0x7FFFFFFFull : x);
+}
+
+// Lane I of each 16 lanes, in all of them (a move on the vector ALU: no trip through LDS).
+template <int I>
+__device__ inline uint32_t bcast16(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + I, 0xf, 0xf, false);
+}
+
+// The 16 lanes of group gr (uniform, 0..3), in all four groups.
+__device__ inline uint32_t group16(uint32_t v, int gr) {
+  const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);  // both halves as the lower one, as the upper
+  const uint32_t u = (gr & 2) ? h[1] : h[0];
+  const auto q = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return (gr & 1) ? q[1] : q[0];
+}
+
+// f(0), f(1), ... with the index a constant, until one returns false
+template <int I, class Fn>
+__device__ inline void pivot_steps(Fn& f) {
+  if constexpr (I < SB_MAXM)
+    if (f(std::integral_constant<int, I>{})) pivot_steps<I + 1>(f);
+}
+
 template <bool MERS>
 __global__ void __launch_bounds__(LEAF_NT) k_mbasis_leaf(const uint32_t* __restrict__ G, int64_t ldg, int m, int n,
-                                                         int sg, int32_t* __restrict__ d, uint32_t* __restrict__ M,
+                                                         int sg, const int32_t* __restrict__ d_in,
+                                                         int32_t* __restrict__ d_out, uint32_t* __restrict__ M,
                                                          int64_t sm, Field F) {
-  constexpr int LC = SB_LEAF + 1;
-  __shared__ uint32_t Ms[2][SB_MAXM][SB_MAXM][LC];
-  __shared__ uint32_t Gs[SB_MAXM][SB_MAXN][SB_LEAF + 1];  // padded: the 8 columns fall in different banks
-  __shared__ uint32_t Dl[SB_MAXM][SB_MAXN];      // residual coefficient, reduced in place
-  __shared__ __align__(16) uint32_t T[SB_MAXM][SB_MAXM];  // this order's row transformation
-  __shared__ int dl[SB_MAXM];
-  __shared__ uint32_t sc[SB_MAXM];              // scale of each row from fraction-free elimination
-  __shared__ int order[SB_MAXM];                // rows by (shifted degree, index)
-  __shared__ uint32_t rinfo[SB_MAXM][2];        // per row: first nonzero unused column, its value
-  const int tid = threadIdx.x;
+  __shared__ __align__(16) uint32_t Rs[2][SB_LEAF * LEAF_RJ];
+  __shared__ uint32_t Ms[2][(SB_LEAF + 1) * LEAF_MJ];
+  __shared__ __align__(16) uint32_t Ts[2][SB_MAXM * LEAF_TR];
+  __shared__ uint32_t piv_s[2];
+  __shared__ uint32_t sc[SB_MAXM];  // scale of each row from fraction-free elimination
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+  const int mc = blockIdx.x;  // this workgroup's column of M
   for (int i = tid; i < SB_MAXM * SB_MAXN * SB_LEAF; i += LEAF_NT) {
-    int r = i / (SB_MAXN * SB_LEAF), c = (i / SB_LEAF) % SB_MAXN, k = i % SB_LEAF;
-    Gs[r][c][k] = (r < m && c < n && k < sg) ? G[(int64_t)(r * n + c) * ldg + k] : 0u;
+    const int k = i % SB_LEAF, c = i / SB_LEAF % SB_MAXN, r = i / (SB_LEAF * SB_MAXN);
+    Rs[0][k * LEAF_RJ + r * SB_MAXN + c] = (r < m && c < n && k < sg) ? G[(int64_t)(r * n + c) * ldg + k] : 0u;
   }
-  for (int i = tid; i < SB_MAXM * SB_MAXM * LC; i += LEAF_NT) {  // both buffers: coefficients above the degree stay 0
-    int r = i / (SB_MAXM * LC), c = (i / LC) % SB_MAXM, k = i % LC;
-    Ms[0][r][c][k] = (r == c && k == 0) ? 1u : 0u;
-    Ms[1][r][c][k] = 0u;
-  }
-  if (tid < m) {
-    dl[tid] = d[tid];
-    sc[tid] = 1u;
+  for (int i = tid; i < (SB_LEAF + 1) * LEAF_MJ; i += LEAF_NT) {  // both: coefficients above the degree stay 0
+    Ms[0][i] = i == mc ? 1u : 0u;
+    Ms[1][i] = 0u;
   }
   __syncthreads();
-  int cur = 0;
-  for (int k = 0; k < sg; ++k) {
-    // residual [x^k](M G): eight lanes per entry, each over an eighth of the inner index; the
-    // eight reduced parts meet through shuffles, each sum of two residues reduced at once
-    {
-      const int o = tid >> 3, part8 = tid & 7;
-      Acc96<MERS> acc;
-      const int r = o / SB_MAXN, c = o % SB_MAXN;
-      if (r < m && c < n) {
-        for (int q = part8; q < m; q += 8) {
-#pragma unroll 8
-          for (int j = 0; j <= k; ++j) acc.add((uint64_t)Ms[cur][r][q][j] * Gs[q][c][k - j]);
-        }
-      }
-      uint32_t v = (r < m && c < n) ? acc.reduce(F) : 0u;
+
+  if (wave < LEAF_EW) {
+    __builtin_amdgcn_s_setprio(3);
+    // this lane: position pos of the order's sequence of rows, columns g and g + 4 of the residual, col of T
+    const int pos = lane & 15, g = lane >> 4, col = 4 * wave + g;
+    int32_t deg = pos < m ? d_in[pos] : 0;  // of row pos
+    // the row at this lane's position: rows by increasing shifted degree, ties by index, those past m last
+    auto row_order = [&] {
+      int before = 0;  // rows 4g .. 4g + 3 that come before row pos
 #pragma unroll
-      for (int sh = 1; sh < 8; sh <<= 1) {
-        const uint32_t t = v + (uint32_t)__shfl_xor((int)v, sh);  // below 2p < 2^32
-        v = t >= F.p ? t - F.p : t;
+      for (int z = 0; z < 4; ++z) {
+        const int j = 4 * g + z, dj = __shfl(deg, j);
+        before += j < m && (pos >= m || dj < deg || (dj == deg && j < pos));
       }
-      if (part8 == 0 && r < m && c < n) Dl[r][c] = v;
-      // the wave holds row r's residual (lane 8c, column c): its first nonzero column and value
-      const uint64_t bal = __ballot(part8 == 0 && r < m && c < n && v != 0u);
-      const int f = bal ? __builtin_ctzll(bal) / 8 : -1;
-      const uint32_t fv = (uint32_t)__shfl((int)v, f < 0 ? 0 : 8 * f);
-      if ((tid & (WAVE - 1)) == 0 && r < m) {
-        rinfo[r][0] = (uint32_t)f;
-        rinfo[r][1] = fv;
-      }
-    }
-    // (no barrier here: the row order reads only the degrees; the barrier after it covers both)
-    // Echelon form of the residual, rows by increasing shifted degree (ties by
-    // index), right-looking: when a row keeps a nonzero residual it becomes a
-    // pivot (column: its first nonzero entry) and every later row is reduced by
-    // it at once, so each row meets the pivots before it in the order they were
-    // found, as in the one-row-at-a-time elimination. T accumulates the row
-    // combinations; pivot rows are multiplied by x below.
-    // row order: the position of row i is the number of rows before it by
-    // (shifted degree, index)
-    if (tid < m) {
-      const int di = dl[tid];
-      int pos = 0;
-      for (int j = 0; j < m; ++j) {
-        const int dj = dl[j];
-        pos += (dj < di) || (dj == di && j < tid);
-      }
-      order[pos] = tid;
-    }
-    for (int idx = tid; idx < m * m; idx += LEAF_NT) T[idx / m][idx % m] = (idx / m == idx % m) ? 1u : 0u;
-    __syncthreads();
-    // Fraction free: row_j <- pv row_j - x_j row_i is the oracle's
-    // row_j - (x_j / pv) row_i times pv. The rows of M (and so of the residual)
-    // stay scaled by the product sc[j] of these factors from order to order;
-    // the scales are divided out once, when the leaf writes its basis. The
-    // pivot column of the later rows becomes zero and is never written: the
-    // lanes read it in place, and the scans skip the columns of earlier pivots.
-    // Every lane keeps the row order in registers (indexed by the unrolled pivot counter below) and
-    // works on one fixed entry of [residual | T] for the whole order: half a wave per row (lane lcol
-    // < 8 a residual column, 8 <= lcol < 24 a column of T), so a row's lanes trade values by
-    // shuffles. The lane's own entry stays in a register (no other lane writes it) and goes to LDS
-    // for the pivot steps of later rows; the scale of a row is kept by its lane 0. Every row's first
-    // nonzero unused column and its value (rinfo, by row) come from the residual phase and, after
-    // each pivot step, from the lanes of every later row, so a pivot step reads two words and the
-    // lane's column of the pivot row, and a row left with zeros costs one read and no barrier.
-    int ord[SB_MAXM];
-#pragma unroll
-    for (int q = 0; q < SB_MAXM; ++q) ord[q] = q < m ? order[q] : 0;
-    constexpr int EW = WAVE / 2;
-    static_assert(SB_MAXN + SB_MAXM <= EW && SB_MAXM * EW <= LEAF_NT && SB_MAXN <= 32, "lanes of the elimination");
-    const int lp = tid / EW, lcol = tid % EW;
-    const bool el_wave = tid < SB_MAXM * EW;  // whole waves
-    const bool lane_on = el_wave && lp < m && (lcol < SB_MAXN ? lcol < n : lcol - SB_MAXN < m);
-    const int lj = lane_on ? order[lp] : 0;
-    const int rowbase = tid & ~(EW - 1);
-    uint32_t own = 0u, scr = 0u;
-    if (lane_on) {
-      own = lcol < SB_MAXN ? Dl[lj][lcol] : T[lj][lcol - SB_MAXN];
-      if (lcol == 0) scr = sc[lj];
-    }
-    uint32_t used = 0, pivmask = 0;  // pivot columns and pivot rows so far (the same in every lane)
-    // rinfo of the rows at positions after `after`, from their lanes (called by whole waves; the rows
-    // at earlier positions are left alone, since slower waves may still read the pivot row's)
-    auto publish = [&](int after) {
-      const uint64_t bal = __ballot(lane_on && lcol < SB_MAXN && !((used >> lcol) & 1u) && own != 0u);
-      const uint32_t rm = (uint32_t)(bal >> (tid & EW)) & ((1u << SB_MAXN) - 1u);
-      const int f = rm ? __builtin_ctz(rm) : -1;
-      const uint32_t fv = (uint32_t)__shfl((int)own, rowbase + (f < 0 ? 0 : f));
-      if (lane_on && lcol == 0 && lp > after) {
-        rinfo[lj][0] = (uint32_t)f;
-        rinfo[lj][1] = fv;
-      }
+      const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)before, (uint32_t)before, false, false);
+      const uint32_t u = h[0] + h[1];
+      const auto q = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+      const int at = pos < m ? (int)(q[0] + q[1]) : pos;
+      return __builtin_amdgcn_ds_permute((at + 16 * g) * 4, pos);  // row pos goes to lane `at`
     };
-#pragma unroll
-    for (int oi = 0; oi < SB_MAXM; ++oi) {
-      if (oi >= m) break;
-      const int i = ord[oi];
-      const int first = (int)rinfo[i][0];
-      const uint32_t pv = rinfo[i][1];
-      const uint32_t prv = lane_on ? (lcol < SB_MAXN ? Dl[i][lcol] : T[i][lcol - SB_MAXN]) : 0u;
-      if (first < 0) continue;  // the same answer in every lane
-      used |= 1u << first;
-      pivmask |= 1u << i;
-      const uint32_t x = (uint32_t)__shfl((int)own, rowbase + first);  // this row's entry in the pivot column
-      if (lane_on && lp > oi && x) {
-        if (lcol == 0) scr = fmul(scr, pv, F);
-        if (lcol >= SB_MAXN || !((used >> lcol) & 1u)) {  // neither this pivot's column nor an earlier one
-          const uint32_t v = fmul(pv, own, F) + fmul(F.p - x, prv, F);
-          own = v >= F.p ? v - F.p : v;
-          if (lcol < SB_MAXN) Dl[lj][lcol] = own;
-          else T[lj][lcol - SB_MAXN] = own;
-        }
-      }
-      if (el_wave) publish(oi);
-      __syncthreads();
-    }
-    if (lane_on && lcol == 0) sc[lj] = scr;
-    if (tid < m && ((pivmask >> tid) & 1u)) dl[tid] += 1;
-    // (no barrier here: the update reads T, complete at the last pivot's barrier, and takes the
-    // pivot rows from pivmask; the scales and degrees are next read after the update's barrier)
-    // M <- diag(x^piv) T M: four lanes per entry (i, c), each over every fourth coefficient, T's row
-    // in registers. M has degree <= k before order k, so only coefficients 0..k+1 change (the
-    // buffers hold zeros above). The 64 lanes of a wave share the row i, so T's zero entries (rows
-    // no pivot was combined into) are skipped without divergence.
-    const int nxt = cur ^ 1;
-    {
-      const int e = tid >> 2, j0 = tid & 3;
-      const int i = e / SB_MAXM, c = e % SB_MAXM;
-      if (i < m && c < m) {
-        uint32_t t[SB_MAXM];
-#pragma unroll
-        for (int q4 = 0; q4 < SB_MAXM; q4 += 4) {  // T's row in 16-byte reads
-          typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-          const u32x4_t tv = *(const u32x4_t*)&T[i][q4];
-          t[q4] = q4 < m ? tv.x : 0u;
-          t[q4 + 1] = q4 + 1 < m ? tv.y : 0u;
-          t[q4 + 2] = q4 + 2 < m ? tv.z : 0u;
-          t[q4 + 3] = q4 + 3 < m ? tv.w : 0u;
-        }
-        const int sh = (int)((pivmask >> i) & 1u);
-        for (int j = j0; j <= k + 1 && j < LC; j += 4) {
-          const int js = j - sh;
-          uint32_t out = 0;
-          if (js >= 0 && js <= k) {
-            Acc96<MERS> acc;
-            if (MERS) {  // four products of residues below 2^31 add below 2^64: one fold per four
-#pragma unroll
-              for (int q0 = 0; q0 < SB_MAXM; q0 += 4) {
-                uint64_t g = 0;
-#pragma unroll
-                for (int q = q0; q < q0 + 4; ++q)
-                  if (q < m && t[q]) g += (uint64_t)t[q] * Ms[cur][q][c][js];
-                acc.lo += (g & 0x7FFFFFFFull) + (g >> 31);
-              }
-            } else {
-#pragma unroll
-              for (int q = 0; q < SB_MAXM; ++q)
-                if (q < m && t[q]) acc.add((uint64_t)t[q] * Ms[cur][q][c][js]);
-            }
-            out = acc.reduce(F);
+    int row = row_order();
+    uint32_t D0 = Rs[0][row * SB_MAXN + g], D1 = Rs[0][row * SB_MAXN + g + 4];
+    for (int k = 0;; ++k) {
+      if (k < sg) {
+        // Echelon form of the residual, right-looking: when a row keeps a nonzero residual it becomes a
+        // pivot (column: its first nonzero entry) and every later row is reduced by it at once. Fraction
+        // free: row_j <- pv row_j - x_j row_i is the oracle's row_j - (x_j / pv) row_i times pv. The rows
+        // stay scaled by the product of these factors, which is T's diagonal, from order to order; the
+        // scales are divided out once, when the leaf writes its basis.
+        uint32_t t = row == col ? 1u : 0u, pivots = 0;
+        uint64_t b0 = __ballot(D0 != 0u), b1 = __ballot(D1 != 0u);
+        auto step = [&](auto index) {
+          constexpr int oi = decltype(index)::value;
+          constexpr uint64_t row_oi = 0x0001000100010001ull << oi, from_oi = 0x0001000100010001ull * (0x10000u - (1u << oi));
+          if (((b0 | b1) & from_oi) == 0) return false;  // what is left is zero
+          const uint64_t r0 = b0 & row_oi, r1 = b1 & row_oi, r = r0 ? r0 : r1;
+          if (r == 0) return true;
+          const uint32_t x = group16(r0 ? D0 : D1, __builtin_ctzll(r) >> 4);  // this row's entry in the pivot column
+          const uint32_t pv = bcast16<oi>(x), p0 = bcast16<oi>(D0), p1 = bcast16<oi>(D1), pt = bcast16<oi>(t);
+          if (pos > oi && x) {
+            const uint32_t nx = F.p - x;
+            D0 = fred<MERS>((uint64_t)pv * D0 + (uint64_t)nx * p0, F);
+            D1 = fred<MERS>((uint64_t)pv * D1 + (uint64_t)nx * p1, F);
+            t = fred<MERS>((uint64_t)pv * t + (uint64_t)nx * pt, F);
           }
-          Ms[nxt][i][c][j] = out;
+          pivots |= 1u << __builtin_amdgcn_readlane(row, oi);
+          b0 = __ballot(D0 != 0u);
+          b1 = __ballot(D1 != 0u);
+          return true;
+        };
+        pivot_steps<0>(step);
+        const uint32_t below = __popc(pivots & ((1u << col) - 1u)), npiv = __popc(pivots);
+        const bool pc = (pivots >> col) & 1u;
+        const uint32_t slot = pc ? below : npiv + (uint32_t)col - below;  // the slots past the last pivot hold 0
+        if (slot < (uint32_t)LEAF_TD) Ts[k & 1][row * LEAF_TR + slot] = pc && row != col ? t : 0u;
+        if (row == col) Ts[k & 1][row * LEAF_TR + LEAF_TD] = t;
+        if (tid == 0) piv_s[k & 1] = pivots;
+        deg += (int)((pivots >> pos) & 1u);
+        row = row_order();
+      }
+      __syncthreads();
+      if (k >= sg) break;
+      // the next residual coefficient: T's row times coefficient k + 1 of R, or coefficient k for a pivot row,
+      // which is multiplied by x
+      if (k + 1 < sg) {
+        typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+        uint32_t pm = (uint32_t)__builtin_amdgcn_readfirstlane((int)piv_s[k & 1]);
+        const uint32_t* tr = &Ts[k & 1][row * LEAF_TR];
+        const uint32_t* rc = &Rs[k & 1][(k + 1 - (int)((pm >> row) & 1u)) * LEAF_RJ + g];
+        Acc96<MERS> a0, a1;
+        const uint32_t td = tr[LEAF_TD];
+        a0.add((uint64_t)td * rc[row * SB_MAXN]);
+        a1.add((uint64_t)td * rc[row * SB_MAXN + 4]);
+#pragma unroll
+        for (int q0 = 0; q0 < SB_MAXN; q0 += 4) {
+          const u32x4_t tv = *(const u32x4_t*)(tr + q0);
+          const uint32_t tq[4] = {tv.x, tv.y, tv.z, tv.w};
+          uint64_t s0 = 0, s1 = 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const uint32_t* rv = rc + (pm ? __builtin_ctz(pm) : 0) * SB_MAXN;
+            pm &= pm - 1u;
+            if (MERS) {  // four products of residues below 2^31 add below 2^64
+              s0 += (uint64_t)tq[q] * rv[0];
+              s1 += (uint64_t)tq[q] * rv[4];
+            } else {
+              a0.add((uint64_t)tq[q] * rv[0]);
+              a1.add((uint64_t)tq[q] * rv[4]);
+            }
+          }
+          if (MERS) {
+            a0.add(s0);
+            a1.add(s1);
+          }
         }
+        D0 = a0.reduce(F);
+        D1 = a1.reduce(F);
       }
     }
-    cur = nxt;
-    __syncthreads();
-  }
-  // divide out the row scales: all inverses from one exponentiation (prefix
-  // products, one inverse, and back)
-  if (tid == 0) {
-    uint32_t pre[SB_MAXM + 1];
-    pre[0] = 1;
-    for (int j = 0; j < m; ++j) pre[j + 1] = fmul(pre[j], sc[j], F);
-    uint32_t inv = finv(pre[m], F);
-    for (int j = m - 1; j >= 0; --j) {
-      const uint32_t ij = fmul(inv, pre[j], F);
-      inv = fmul(inv, sc[j], F);
-      sc[j] = ij;
+    if (mc == 0 && wave == 0 && g == 0 && pos < m) d_out[pos] = deg;
+  } else {
+    // rows 4 rg .. 4 rg + 3 of columns u = part * 64 + lane, + 64 LEAF_AW / 4, ...: first the 8 columns of R's
+    // coefficients from k on, then M's coefficients up to k
+    const int rg = (wave - LEAF_EW) % 4, part = (wave - LEAF_EW) / 4;
+    uint32_t scale = 1u;  // of row 4 rg + r in the lane of its diagonal entry
+    for (int k = 0;; ++k) {
+      if (k > 0) {
+        const int o = k - 1, b = o & 1, nb = b ^ 1;  // T of order o: buffers b to nb
+        const int tv = (int)Ts[b][rg * 4 * LEAF_TR + min(lane, 4 * LEAF_TR - 1)];  // four rows of T
+        const uint32_t pivots = (uint32_t)__builtin_amdgcn_readfirstlane((int)piv_s[b]);
+        scale = fred<MERS>((uint64_t)scale * (uint32_t)tv, F);
+        const int nr = SB_MAXN * (sg - o), nu = nr + o + 1;
+        // (every lane takes every turn, so that readlane finds all of T's rows; the lanes past the end write nothing)
+        for (int u0 = part * WAVE; u0 < nu; u0 += WAVE * LEAF_AW / 4) {
+          const bool on = u0 + lane < nu;
+          const int u = on ? u0 + lane : u0;
+          const bool inr = u < nr;
+          const int j = inr ? o + u / SB_MAXN : u - nr, c = inr ? u % SB_MAXN : 0;
+          const int at = inr ? j * LEAF_RJ + c : j * LEAF_MJ, qs = inr ? 3 : 0;  // log2 of the stride over rows
+          const uint32_t* src = (inr ? Rs[b] : Ms[b]) + at;
+          uint32_t* dst = (inr ? Rs[nb] : Ms[nb]) + at;
+          uint32_t po[SB_MAXN], own[4], pm = pivots;
+#pragma unroll
+          for (int q = 0; q < SB_MAXN; ++q) {
+            po[q] = src[(pm ? __builtin_ctz(pm) : 0) << qs];
+            pm &= pm - 1u;
+          }
+#pragma unroll
+          for (int r = 0; r < 4; ++r) own[r] = src[(rg * 4 + r) << qs];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int i = rg * 4 + r;
+            auto tq = [&](int q) { return (uint64_t)(uint32_t)__builtin_amdgcn_readlane(tv, r * LEAF_TR + q); };
+            Acc96<MERS> acc;
+            acc.add(tq(LEAF_TD) * own[r]);
+#pragma unroll
+            for (int q = 0; q < SB_MAXN; q += 4) {
+              if (MERS) {
+                acc.add(tq(q) * po[q] + tq(q + 1) * po[q + 1] + tq(q + 2) * po[q + 2] + tq(q + 3) * po[q + 3]);
+              } else {
+#pragma unroll
+                for (int z = q; z < q + 4; ++z) acc.add(tq(z) * po[z]);
+              }
+            }
+            const uint32_t v = acc.reduce(F);
+            if (!on) continue;
+            if ((pivots >> i) & 1u) {  // times x
+              if (!inr || j + 1 < sg) dst[(inr ? LEAF_RJ : LEAF_MJ) + (i << qs)] = v;
+              if (!inr && j == 0) dst[i] = 0u;
+            } else {
+              dst[i << qs] = v;
+            }
+          }
+        }
+      }
+      __syncthreads();
+      if (k >= sg) break;
     }
+    if (part == 0 && lane < 4 * LEAF_TR && lane % LEAF_TR == LEAF_TD) sc[rg * 4 + lane / LEAF_TR] = scale;
   }
   __syncthreads();
-  for (int idx = tid; idx < m * m * (sg + 1); idx += LEAF_NT) {
-    const int i = idx / (m * (sg + 1)), c = (idx / (sg + 1)) % m, j = idx % (sg + 1);
-    M[(int64_t)(i * m + c) * sm + j] = fmul(Ms[cur][i][c][j], sc[i], F);
+  if (tid < SB_MAXM) sc[tid] = finv(sc[tid], F);
+  __syncthreads();
+  for (int idx = tid; idx < m * (sg + 1); idx += LEAF_NT) {
+    const int i = idx / (sg + 1), j = idx % (sg + 1);
+    M[(int64_t)(i * m + mc) * sm + j] = fmul(Ms[sg & 1][j * LEAF_MJ + i], sc[i], F);
   }
-  if (tid < m) d[tid] = dl[tid];
 }
 
 // G = [S(x); -I] as 2s x s entries of L coefficients from S (L x s x s, dtype residues mod p).
@@ -797,7 +825,8 @@ struct SbCtx {
   Field F;
   int m, n;
   hipStream_t st;
-  int32_t* d_dev;       // m shifted degrees on the device: the leaves read and update them there
+  int32_t* d_dev;       // m shifted degrees on the device: a leaf reads them here and writes the
+  int32_t* d_next;      // new ones there, and the two change places
   bool d_host = true;   // the host copy of the degrees is current
 };
 
@@ -821,12 +850,14 @@ static int64_t pmbasis(SbCtx& X, const uint32_t* G, int64_t sg, int64_t sigma, s
                        int64_t sm) {
   const int m = X.m, n = X.n;
   if (sigma <= SB_LEAF) {
+    const dim3 grid((unsigned)m);
     if (X.F.mersenne)
-      hipLaunchKernelGGL((k_mbasis_leaf<true>), dim3(1), dim3(LEAF_NT), 0, X.st, G, sg, m, n, (int)sigma, X.d_dev, M,
-                         sm, X.F);
+      hipLaunchKernelGGL((k_mbasis_leaf<true>), grid, dim3(LEAF_NT), 0, X.st, G, sg, m, n, (int)sigma, X.d_dev,
+                         X.d_next, M, sm, X.F);
     else
-      hipLaunchKernelGGL((k_mbasis_leaf<false>), dim3(1), dim3(LEAF_NT), 0, X.st, G, sg, m, n, (int)sigma, X.d_dev, M,
-                         sm, X.F);
+      hipLaunchKernelGGL((k_mbasis_leaf<false>), grid, dim3(LEAF_NT), 0, X.st, G, sg, m, n, (int)sigma, X.d_dev,
+                         X.d_next, M, sm, X.F);
+    std::swap(X.d_dev, X.d_next);
     FFX_HIP(hipGetLastError());
     X.d_host = false;
     return sigma + 1;
@@ -913,19 +944,20 @@ void sigma_basis(uint32_t p, int m, int n, int64_t sigma, const uint32_t* G, int
   std::vector<int32_t> d(shift, shift + m);
   for (int32_t v : d)
     if (v < 0 || v > (1 << 28)) fail(FFX_EINVAL, "shift %d outside [0, 2^28]", v);
-  SbCtx X{make_field(p), m, n, st, nullptr};
-  if (hipMallocAsync((void**)&X.d_dev, SB_MAXM * sizeof(int32_t), st) != hipSuccess)
+  int32_t* degrees = nullptr;
+  if (hipMallocAsync((void**)&degrees, 2 * SB_MAXM * sizeof(int32_t), st) != hipSuccess)
     fail(FFX_ENOMEM, "order basis workspace allocation failed");
+  SbCtx X{make_field(p), m, n, st, degrees, degrees + SB_MAXM};
   try {
     FFX_HIP(hipMemcpyAsync(X.d_dev, d.data(), m * sizeof(int32_t), hipMemcpyHostToDevice, st));
     const int64_t len = pmbasis(X, G, ldg, sigma, d, M, ldm);
     if (len < ldm) FFX_HIP(hipMemset2DAsync(M + len, ldm * 4, 0, (ldm - len) * 4, (size_t)m * m, st));
     host_degrees(X, d);
   } catch (...) {
-    (void)hipFreeAsync(X.d_dev, st);
+    (void)hipFreeAsync(degrees, st);
     throw;
   }
-  (void)hipFreeAsync(X.d_dev, st);
+  (void)hipFreeAsync(degrees, st);
   FFX_HIP(hipStreamSynchronize(st));
   std::copy(d.begin(), d.end(), d_out);
 }
