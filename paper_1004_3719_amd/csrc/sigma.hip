@@ -14,9 +14,9 @@
 //
 // Large polynomial matrix products go through number-theoretic transforms over
 // three word-size primes and a CRT (the paper's DFT multiplication; see the
-// NTT section below); the small ones, where the transforms' passes cost more
-// than the convolution, are schoolbook convolutions on the vector ALU.
-// A workgroup computes 256 consecutive coefficients of one entry; for each
+// NTT section below); smaller ones are schoolbook convolutions, on the matrix
+// cores in bytes (see k_polymul_mx), or for the fewest rows on the vector ALU.
+// There a workgroup computes 256 consecutive coefficients of one entry; for each
 // inner index q and each 256-coefficient chunk of A it stages the chunk of A and
 // the 511 coefficients of B that the tile needs in LDS, and every lane adds
 // 256 products into a 96-bit accumulator (64-bit sum plus a carry count), so a
@@ -784,11 +784,224 @@ static bool polymul_ntt(const uint32_t* A, int64_t sa, int64_t la, const uint32_
   return true;
 }
 
+// Matrix-core products. A residue, taken in (-p/2, p/2), is four signed bytes
+// d_l, x = sum_l d_l 256^l, so a product of two polynomial matrices is sixteen
+// convolutions of matrices of bytes, of which those of equal l + l' share an
+// accumulator, and one 16 x 16 x 64 instruction takes four coefficients j of A
+// against B's coefficients t - j: rows r, columns c, and for the inner index
+// the pairs (j, q). A column count below 16 leaves room for several t.
+//
+// k_pm_bytes writes the operands as byte planes [l][coefficient][row or column][q]
+// (q in 16 consecutive bytes: one lane's operand), B's with zeros around the
+// coefficients it has, so that k_polymul_mx has no conditions in its loop. A
+// wave computes T coefficients t four apart: as j advances by four, coefficient
+// t + 4 needs the operand of B that t has just used, so a step loads one operand
+// of A and one of B for 16 T instructions. The four waves of a workgroup split the
+// range of j and add up their residues in LDS.
+//
+// The vector ALU does at most one 31-bit multiply-add per lane in 22 cycles
+// (a product at a quarter of the rate and its folds), 3 per cycle and SIMD; the
+// matrix cores take 64. The 508 products of a 16 x 8 order basis of 8,003 orders
+// took 19.4 ms on the vector ALU and take 5.5 ms, 2.4 of them for the planes.
+//
+// The line is at four rows, below which most of an instruction is padding: a basis
+// of 8,003 orders with m = 2 takes 21.5 ms this way and 20.5 on the vector ALU,
+// with m = 4 22.7 and 23.0, one of 3,001 orders with m = 5 8.9 and 9.3.
+constexpr int MX_MINQ = 4;
+typedef int32_t i32x4_t __attribute__((ext_vector_type(4)));
+constexpr int MX_FLUSH = 256;  // steps of 4 coefficients an accumulator takes: 4 * 16 * 1024 products of at most 2^14
+
+struct MxField {
+  Field F;
+  uint64_t bias;  // a multiple of p, at least 2^55: makes sums of byte products positive
+  uint32_t r32;   // 2^32 mod p
+};
+
+__device__ inline void mx_bytes(const uint32_t* x, uint32_t p, uint32_t* plane) {
+  uint32_t d[4];  // the four signed bytes of each residue
+#pragma unroll
+  for (int k = 0; k < 4; ++k) d[k] = ((x[k] > p / 2 ? x[k] - p : x[k]) + 0x80808080u) ^ 0x80808080u;
+#pragma unroll
+  for (int l = 0; l < 4; ++l)
+    plane[l] = (d[0] >> (8 * l) & 0xffu) | (d[1] >> (8 * l) & 0xffu) << 8 | (d[2] >> (8 * l) & 0xffu) << 16 |
+               (d[3] >> (8 * l)) << 24;
+}
+
+// pa: 4 planes of na coefficients, [16 rows][16 q] bytes each; pb: 4 planes of nb coefficients from ub on,
+// [1 << cl columns][16 q] bytes each
+__global__ void __launch_bounds__(256) k_pm_bytes(const uint32_t* __restrict__ A, int64_t sa, int64_t la, int64_t na,
+                                                  int R, const uint32_t* __restrict__ B, int64_t sb, int64_t lb,
+                                                  int64_t ub, int64_t nb, int NC, int cl, int Q, uint32_t p,
+                                                  uint32_t* __restrict__ pa, uint32_t* __restrict__ pb) {
+  const int64_t ia = (na + 15) / 16 * 1024, ib = (nb + 15) / 16 << (cl + 6);  // items: four q of a row or column
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ia + ib; i += (int64_t)gridDim.x * 256) {
+    // 16 coefficients by 4 groups of q to a wave: runs of 64 bytes in, of 16 bytes out
+    const bool isa = i < ia;
+    const int64_t k = isa ? i : i - ia, n = isa ? na : nb;
+    const int l = isa ? 4 : cl;
+    const int64_t blk = k >> (6 + l);              // block of 16 coefficients
+    const int in = (int)(k & ((64 << l) - 1));     // within it: [row or column][q group][coefficient]
+    const int rc = in >> 6, qg = in >> 4 & 3;
+    const int64_t j = blk * 16 + (in & 15);
+    if (j >= n) continue;
+    const int64_t u = isa ? j : ub + j;
+    const bool on = u >= 0 && u < (isa ? la : lb) && rc < (isa ? R : NC);
+    uint32_t x[4], plane[4];
+#pragma unroll
+    for (int z = 0; z < 4; ++z) {
+      const int q = 4 * qg + z;
+      x[z] = on && q < Q ? (isa ? A[(int64_t)(rc * Q + q) * sa + u] : B[(int64_t)(q * NC + rc) * sb + u]) : 0u;
+    }
+    mx_bytes(x, p, plane);
+    uint32_t* out = isa ? pa : pb;
+#pragma unroll
+    for (int z = 0; z < 4; ++z) out[(((int64_t)z * n + j << l) + rc) * 4 + qg] = plane[z];
+  }
+}
+
+template <bool MERS, int T>
+__global__ void __launch_bounds__(256) k_polymul_mx(const i32x4_t* __restrict__ pa, int64_t la, int64_t na,
+                                                    const i32x4_t* __restrict__ pb, int64_t lb, int64_t ub, int64_t nb,
+                                                    uint32_t* __restrict__ C, int64_t sc, int64_t k0, int64_t len,
+                                                    int R, int NC, int cl, MxField P) {
+  __shared__ uint32_t sums[4][4 * T][WAVE];
+  const int lane = threadIdx.x & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const int row = lane & 15, jj = lane >> 4, c = row & ((1 << cl) - 1), tt = row >> cl;
+  const int64_t tb = (int64_t)(blockIdx.x >> 2) * (4 * T << (4 - cl)) + (blockIdx.x & 3);  // the tile's first coefficient
+  const int64_t t0 = tb + tt * 4 * T;  // this lane's column's
+  const int64_t tlast = k0 + tb + 4 * T * ((16 >> cl) - 1) + 4 * (T - 1);
+  // steps of four j that meet coefficients of B
+  const int64_t s0 = std::max<int64_t>(0, k0 + tb - (lb - 1)) / 4, s1 = std::min<int64_t>(la - 1, tlast) / 4 + 1;
+  const int64_t ns = std::max<int64_t>(0, s1 - s0), w0 = s0 + ns * wave / 4, w1 = s0 + ns * (wave + 1) / 4;
+  uint32_t res[T][4];
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) res[i][v] = 0u;
+  auto load_a = [&](int64_t s, i32x4_t* a) {
+#pragma unroll
+    for (int l = 0; l < 4; ++l) a[l] = pa[(l * na + 4 * s + jj) * 16 + row];
+  };
+  auto load_b = [&](int64_t s, int i, i32x4_t* b) {
+#pragma unroll
+    for (int l = 0; l < 4; ++l) b[l] = pb[((l * nb + (k0 + t0 + 4 * i - 4 * s - jj - ub)) << cl) + c];
+  };
+  for (int64_t f0 = w0; f0 < w1; f0 += MX_FLUSH) {
+    const int64_t f1 = std::min<int64_t>(w1, f0 + MX_FLUSH);
+    i32x4_t acc[T][7], a[4], b[T][4], an[4], bn[4];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+      for (int w = 0; w < 7; ++w) acc[i][w] = (i32x4_t)(0);
+    load_a(f0, a);
+#pragma unroll
+    for (int i = 0; i < T; ++i) load_b(f0, i, b[i]);
+#pragma unroll T
+    for (int64_t s = f0; s < f1; ++s) {
+      const int64_t sn = std::min<int64_t>(s + 1, f1 - 1);
+      load_a(sn, an);
+      load_b(sn, 0, bn);
+#pragma unroll
+      for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+          for (int y = 0; y < 4; ++y)
+            acc[i][x + y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[x], b[i][y], acc[i][x + y], 0, 0, 0);
+#pragma unroll
+      for (int i = T - 1; i > 0; --i)
+#pragma unroll
+        for (int l = 0; l < 4; ++l) b[i][l] = b[i - 1][l];
+#pragma unroll
+      for (int l = 0; l < 4; ++l) a[l] = an[l], b[0][l] = bn[l];
+    }
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t lo = (int64_t)acc[i][0][v] + ((int64_t)acc[i][1][v] << 8) + ((int64_t)acc[i][2][v] << 16) +
+                           ((int64_t)acc[i][3][v] << 24);  // below 2^55 in magnitude
+        const int64_t hi = (int64_t)acc[i][4][v] + ((int64_t)acc[i][5][v] << 8) + ((int64_t)acc[i][6][v] << 16);
+        uint32_t x;
+        if (MERS) x = fred<true>((uint64_t)(lo + 2 * hi) + P.bias, P.F);  // 2^32 = 2 mod p
+        else
+          x = mod_u64((uint64_t)mod_u64((uint64_t)hi + P.bias, P.F.p, P.F.mu) * P.r32 +
+                          mod_u64((uint64_t)lo + P.bias, P.F.p, P.F.mu),
+                      P.F.p, P.F.mu);
+        const uint32_t sum = res[i][v] + x;
+        res[i][v] = sum >= P.F.p ? sum - P.F.p : sum;
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sums[wave][4 * i + v][lane] = res[i][v];
+  __syncthreads();
+#pragma unroll
+  for (int z = 0; z < T; ++z) {  // a quarter of the tile to each wave
+    const int e = wave * T + z, i = e / 4, v = e % 4;
+    uint32_t sum = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      sum += sums[w][e][lane];
+      sum = sum >= P.F.p ? sum - P.F.p : sum;
+    }
+    const int r = 4 * jj + v;
+    const int64_t t = t0 + 4 * i;
+    if (r < R && c < NC && t < len) C[(int64_t)(r * NC + c) * sc + t] = sum;
+  }
+}
+
+template <int T>
+static void launch_mx(unsigned tiles, const i32x4_t* pa, int64_t la, int64_t na, const i32x4_t* pb, int64_t lb, int64_t ub,
+                      int64_t nb, uint32_t* C, int64_t sc, int64_t k0, int64_t len, int R, int NC, int cl,
+                      const MxField& P, hipStream_t st) {
+  if (P.F.mersenne)
+    hipLaunchKernelGGL((k_polymul_mx<true, T>), dim3(tiles), dim3(256), 0, st, pa, la, na, pb, lb, ub, nb, C, sc, k0,
+                       len, R, NC, cl, P);
+  else
+    hipLaunchKernelGGL((k_polymul_mx<false, T>), dim3(tiles), dim3(256), 0, st, pa, la, na, pb, lb, ub, nb, C, sc, k0,
+                       len, R, NC, cl, P);
+}
+
+// polymul on the matrix cores, any la, lb >= 1
+static void polymul_mx(const uint32_t* A, int64_t sa, int64_t la, const uint32_t* B, int64_t sb, int64_t lb,
+                       uint32_t* C, int64_t sc, int64_t k0, int64_t len, int R, int Q, int NC, const Field& F,
+                       hipStream_t st) {
+  int cl = 0;
+  while ((1 << cl) < NC) ++cl;
+  MxField P{F, (((uint64_t)1 << 55) / F.p + 1) * F.p, (uint32_t)(((uint64_t)1 << 32) % F.p)};
+  // more coefficients to a wave once there is a workgroup for every compute unit
+  const int T = len > (int64_t)2048 << (4 - cl) ? 4 : len > (int64_t)512 << (4 - cl) ? 2 : 1;
+  const int64_t per = (int64_t)4 * T << (4 - cl), blocks = (len + per - 1) / per;
+  const int64_t na = (la + 3) / 4 * 4, ub = k0 - na + 1, nb = k0 + blocks * per - ub;
+  const size_t ba = (size_t)na * 1024, bb = (size_t)nb << (cl + 6);
+  uint8_t* planes = nullptr;
+  if (hipMallocAsync((void**)&planes, ba + bb, st) != hipSuccess)
+    fail(FFX_ENOMEM, "polynomial product workspace allocation failed (%lld and %lld coefficients)", (long long)la,
+         (long long)lb);
+  const int64_t items = (na + 15) / 16 * 1024 + ((nb + 15) / 16 << (cl + 6));
+  hipLaunchKernelGGL(k_pm_bytes, dim3((unsigned)std::min<int64_t>((items + 255) / 256, 4096)), dim3(256), 0, st, A, sa, la,
+                     na, R, B, sb, lb, ub, nb, NC, cl, Q, F.p, (uint32_t*)planes, (uint32_t*)(planes + ba));
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) {
+    const i32x4_t *pa = (const i32x4_t*)planes, *pb = (const i32x4_t*)(planes + ba);
+    const unsigned tiles = (unsigned)(blocks * 4);
+    if (T == 4) launch_mx<4>(tiles, pa, la, na, pb, lb, ub, nb, C, sc, k0, len, R, NC, cl, P, st);
+    else if (T == 2) launch_mx<2>(tiles, pa, la, na, pb, lb, ub, nb, C, sc, k0, len, R, NC, cl, P, st);
+    else launch_mx<1>(tiles, pa, la, na, pb, lb, ub, nb, C, sc, k0, len, R, NC, cl, P, st);
+    e = hipGetLastError();
+  }
+  (void)hipFreeAsync(planes, st);
+  FFX_HIP(e);
+}
+
 static void polymul(const uint32_t* A, int64_t sa, int64_t la, const uint32_t* B, int64_t sb, int64_t lb, uint32_t* C,
                     int64_t sc, int64_t k0, int64_t len, int R, int Q, int NC, const Field& F, hipStream_t st) {
   if (len <= 0) return;
   const int64_t nt = g_ntt_min.load();
   if (nt > 0 && la >= nt && lb >= nt && polymul_ntt(A, sa, la, B, sb, lb, C, sc, k0, len, R, Q, NC, F, st)) return;
+  if (Q >= MX_MINQ) return polymul_mx(A, sa, std::max<int64_t>(la, 1), B, sb, lb, C, sc, k0, len, R, Q, NC, F, st);
   const int64_t tiles = (len + PM_TILE - 1) / PM_TILE;
   if (tiles <= PMS_MAX_TILES && la <= PMS_MAXA && polymul_small_lds(Q, std::max<int64_t>(la, 1)) <= 64 * 1024) {
     const int la1 = (int)std::max<int64_t>(la, 1);

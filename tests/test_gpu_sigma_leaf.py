@@ -53,3 +53,37 @@ def test_leaf(dev, m, n, sig, shift, kind, p):
     Mo, do = osig.mbasis(G, sig, d0, p)
     assert d == do
     assert np.array_equal(M.cpu().numpy().astype(np.int64), Mo)
+
+
+@pytest.mark.parametrize("p", [65521, M31, M31 - 18])
+@pytest.mark.parametrize("m,n,sig,kind", [(4, 1, 65, "top"), (4, 3, 130, "random"), (5, 5, 97, "top"), (7, 2, 200, "random"),
+                                          (9, 8, 129, "sparse"), (13, 4, 260, "random"), (16, 8, 140, "top"),
+                                          (16, 7, 518, "random"), (3, 3, 130, "random")])
+def test_products(dev, m, n, sig, kind, p):
+    """Products at the edges of the matrix-core form: the fewest rows it takes and one below, column
+    counts about the powers of two, ragged lengths, residues at the ends of their range."""
+    from paper_1004_3719_amd import sigma_basis
+    G = series(kind, m, n, sig, p)
+    d0 = [0] * (m - n) + [1] * n
+    M, d = sigma_basis(torch.from_numpy(G.astype(np.int32)).to(dev), p, d0)
+    Mo, do = osig.mbasis(G, sig, d0, p)
+    assert d == do
+    assert np.array_equal(M.cpu().numpy().astype(np.int64), Mo)
+
+
+@pytest.mark.parametrize("p", [65521, M31])
+def test_products_long(dev, p):
+    """Convolutions of thousands of coefficients (several flushes of the byte sums, four coefficients to
+    a wave) against the transforms: the same basis either way."""
+    from paper_1004_3719_amd import ffx, sigma_basis
+    G = torch.from_numpy(series("top", 16, 8, 20000, p).astype(np.int32))
+    G[:, :, 1::2] = torch.from_numpy(series("random", 16, 8, 10000, p).astype(np.int32))
+    G, d0 = G.to(dev), [0] * 8 + [1] * 8
+    try:
+        ffx.set_ntt_threshold(0)
+        M, d = sigma_basis(G, p, d0)
+        ffx.set_ntt_threshold(64)
+        Mt, dt = sigma_basis(G, p, d0)
+    finally:
+        ffx.set_ntt_threshold(1024)
+    assert d == dt and torch.equal(M, Mt)
