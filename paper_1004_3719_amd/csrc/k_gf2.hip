@@ -17,12 +17,17 @@ hipError_t launch_tiles_gf2(const DevMat& A, int64_t mte, const void* X, int64_t
 // entry (a, 32c + b), the parity of the rows j where bit a of U[j] and bit b of
 // word c of (A^i V)[j] are both set.
 //
-// One launch per iteration i, as for residues: workgroup t < ntiles computes
-// its tile's rows of W_{i+1} = A W_i (the product's tile code) and then the
-// XOR over those rows of its share of U^T W_{i+1}, a partial of 32w*w words;
-// GF2_NMID workgroups fold the partials of W_i (written by the previous launch)
-// into GF2_NMID words per pair, and one workgroup folds those of iteration
-// i-1 into S_{i-1}. Partials and folds are double-buffered by parity.
+// One launch per iteration i: workgroup t < ntiles computes its tile's rows of
+// W_{i+1} = A W_i (the product's tile code); one workgroup per 256 rows computes
+// their XOR share of U^T W_i, a partial of 32w*w words; GF2_NMID workgroups fold
+// the partials of W_{i-1} (written by the previous launch) into GF2_NMID words
+// per pair, and one workgroup folds those of iteration i-2 into S_{i-2}. Partials
+// and folds are double-buffered by parity.
+//
+// The product waits for the L2's answers to its gathers and the projection keeps
+// the vector ALU and LDS busy, so they run in workgroups of their own, side by
+// side: 200,000 rows of 15 entries, w = 2: 30.3 us per iteration with each
+// workgroup doing the projection of its tile after its product, 23.8 us now.
 namespace ffx {
 
 constexpr uint32_t GF2_NMID = 64;
@@ -38,53 +43,68 @@ struct Gf2SeqArgs {
   int32_t w;
 };
 
-// Row of slot q of a tile (>= nrows for a padding slot).
-__device__ inline uint32_t gf2_tile_row(const DevMat& A, const Tile& T, uint32_t q) {
-  return (tile_kind(T.kind) == TK_SELL && (T.kind & TF_SORTED)) ? A.perm[T.row0 + q] : T.row0 + q;
-}
-
-// out[p] for the pairs p = a*w + c: XOR over the tile's rows of (bit a of U[row]) * W[row][c]. The
-// tile's rows of U and W are staged in LDS first (sh: 2 * 256 * w words, then 256 for the groups).
-__device__ inline void tile_projection_gf2(const DevMat& A, const Tile& T, const uint32_t* __restrict__ U,
-                                           const uint32_t* W, int w, uint32_t* sh, uint32_t* __restrict__ out) {
-  const int tid = threadIdx.x, npairs = 32 * w * w;
-  const int nq = tile_kind(T.kind) == TK_LONG ? 1 : (int)tile_rows(T.kind);
+// out[a*w + c]: XOR over the nr <= 256 rows from r0 on of (bit a of U[row]) * W[row][c]. The rows of U and
+// W are staged in LDS (su: w words to a row, sw: S, those past w zero); a lane takes one bit a and all of
+// W's words, so a row costs two reads, one bit extraction and an and-xor per word, and where there are
+// fewer than 256 bits, groups of lanes take every ngrp-th row each.
+template <int S>
+__device__ inline void rows_projection_gf2(const uint32_t* __restrict__ U, const uint32_t* __restrict__ W, int64_t r0,
+                                           int nr, int w, uint32_t* sh, uint32_t* __restrict__ out) {
+  struct alignas(S >= 4 ? 16 : 8) Words { uint32_t x[S]; };
+  const int tid = threadIdx.x, nbits = 32 * w;
   uint32_t* su = sh;
-  uint32_t* sw = sh + TILE_THREADS * w;
-  uint32_t* red = sw + TILE_THREADS * w;
-  for (int k = tid; k < nq * w; k += TILE_THREADS) {
-    const uint32_t row = gf2_tile_row(A, T, (uint32_t)(k / w));
-    const int c = k % w;
-    const bool ok = row < A.nrows;
-    su[k] = ok ? U[(int64_t)row * w + c] : 0u;
-    sw[k] = ok ? W[(int64_t)row * w + c] : 0u;
+  Words* sw = (Words*)(sh + TILE_THREADS * w);
+  for (int k = tid; k < nr * w; k += TILE_THREADS) su[k] = U[r0 * w + k];
+  for (int k = tid; k < nr * S; k += TILE_THREADS) {
+    const int c = k % S;
+    ((uint32_t*)sw)[k] = c < w ? W[(r0 + k / S) * w + c] : 0u;
   }
   __syncthreads();
-  if (npairs <= TILE_THREADS) {
-    const int ngrp = TILE_THREADS / npairs, grp = tid / npairs, p = tid % npairs;
-    const int a = p / w, c = p - a * w, ua = a >> 5, ub = a & 31;
-    uint32_t acc = 0;
-    if (grp < ngrp)
-      for (int q = grp; q < nq; q += ngrp) acc ^= (0u - ((su[q * w + ua] >> ub) & 1u)) & sw[q * w + c];
-    red[tid] = grp < ngrp ? acc : 0u;
-    __syncthreads();
-    if (tid < npairs) {
-      uint32_t x = 0;
-      for (int g = 0; g < ngrp; ++g) x ^= red[g * npairs + tid];
-      out[tid] = x;
+  const int ngrp = nbits < TILE_THREADS ? TILE_THREADS / nbits : 1, grp = nbits < TILE_THREADS ? tid / nbits : 0;
+  auto bit_words = [&](int a, uint32_t* acc) {
+    const int ua = a >> 5, ub = a & 31;
+#pragma unroll
+    for (int c = 0; c < S; ++c) acc[c] = 0u;
+#pragma unroll 4
+    for (int q = grp; q < nr; q += ngrp) {
+      const uint32_t on = (uint32_t)((int32_t)(su[q * w + ua] << (31 - ub)) >> 31);  // all ones where the bit is set
+      const Words x = sw[q];
+#pragma unroll
+      for (int c = 0; c < S; ++c) acc[c] ^= on & x.x[c];
     }
-  } else {
-    for (int p = tid; p < npairs; p += TILE_THREADS) {
-      const int a = p / w, c = p - a * w, ua = a >> 5, ub = a & 31;
-      uint32_t acc = 0;
-      for (int q = 0; q < nq; ++q) acc ^= (0u - ((su[q * w + ua] >> ub) & 1u)) & sw[q * w + c];
-      out[p] = acc;
+  };
+  if (nbits >= TILE_THREADS) {
+    for (int a = tid; a < nbits; a += TILE_THREADS) {
+      uint32_t acc[S];
+      bit_words(a, acc);
+#pragma unroll
+      for (int c = 0; c < S; ++c)
+        if (c < w) out[a * w + c] = acc[c];
     }
+    return;
+  }
+  uint32_t acc[S];
+  const int a = tid - grp * nbits;
+  if (grp < ngrp) bit_words(a, acc);
+  __syncthreads();  // the sums take the place of the rows of W
+  if (grp < ngrp) {
+    Words v;
+#pragma unroll
+    for (int c = 0; c < S; ++c) v.x[c] = acc[c];
+    sw[tid] = v;
+  }
+  __syncthreads();
+  for (int p = tid; p < nbits * w; p += TILE_THREADS) {
+    uint32_t x = 0;
+    for (int g = 0; g < ngrp; ++g) x ^= sw[g * nbits + p / w].x[p % w];
+    out[p] = x;
   }
 }
 
-// LDS of tile_projection_gf2.
-inline size_t gf2_projection_lds(int w) { return (size_t)(2 * TILE_THREADS * w + TILE_THREADS) * sizeof(uint32_t); }
+// LDS of rows_projection_gf2.
+inline size_t gf2_projection_lds(int w, int S) { return (size_t)TILE_THREADS * (w + S) * sizeof(uint32_t); }
+// Workgroups of the projection.
+inline uint32_t gf2_projection_blocks(const DevMat& A) { return (A.nrows + TILE_THREADS - 1) / TILE_THREADS; }
 
 // XOR of part[g][p] over g = first, first + stride, ... < nparts, for every pair p.
 __device__ inline void fold_xor(const uint32_t* __restrict__ part, uint32_t first, uint32_t stride, uint32_t nparts,
@@ -96,39 +116,36 @@ __device__ inline void fold_xor(const uint32_t* __restrict__ part, uint32_t firs
   }
 }
 
-// Partials of W_0 = V.
-__global__ __launch_bounds__(TILE_THREADS) void k_seq_first_gf2(DevMat A, Gf2SeqArgs q) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  const Tile T = A.tiles[blockIdx.x];
-  tile_projection_gf2(A, T, q.U, q.W[0], q.w, (uint32_t*)lds, q.part[0] + (int64_t)blockIdx.x * 32 * q.w * q.w);
-}
-
+// Iteration i < L, and i = L for the folds that are left.
 template <int S>
 __global__ __launch_bounds__(TILE_THREADS) void k_seq_step_gf2(DevMat A, Gf2SeqArgs q, int64_t i) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int w = q.w, npairs = 32 * w * w;
-  const uint32_t nt = A.ntiles;
-  if (blockIdx.x >= nt) {
-    const uint32_t r = blockIdx.x - nt;
-    if (r < GF2_NMID) fold_xor(q.part[i & 1], r, GF2_NMID, nt, npairs, q.mid[i & 1] + (int64_t)r * npairs);
-    else if (i > 0) fold_xor(q.mid[(i - 1) & 1], 0, 1, GF2_NMID, npairs, q.S + (i - 1) * (int64_t)npairs);
-    return;
-  }
+  const uint32_t nt = A.ntiles, np = (A.nrows + TILE_THREADS - 1) / TILE_THREADS;
   const bool last = i + 1 == q.L;
-  if (last && !q.Wlast) return;
-  const int32_t* X = (const int32_t*)q.W[i & 1];
-  int32_t* Y = (int32_t*)(last ? q.Wlast : q.W[(i + 1) & 1]);
-  const Tile T = A.tiles[blockIdx.x];
-  switch (tile_kind(T.kind)) {
-    case TK_SELL: sell_tile_q<ArGF2, int32_t, int32_t, S>(A, T, X, w, Y, w, w, 1, 0); break;
-    case TK_LONG: long_tile<ArGF2, int32_t, int32_t, S, 1>(A, T, X, w, Y, w, w, 1, 0, lds); break;
-    default: stream_tile_b<ArGF2, int32_t, int32_t, S>(A, T, X, w, Y, w, w, 1, 0, lds);
+  if (blockIdx.x >= nt + np) {
+    const uint32_t r = blockIdx.x - nt - np;
+    if (r < GF2_NMID) {
+      if (i > 0) fold_xor(q.part[(i - 1) & 1], r, GF2_NMID, np, npairs, q.mid[(i - 1) & 1] + (int64_t)r * npairs);
+    } else if (i > 1) {
+      fold_xor(q.mid[i & 1], 0, 1, GF2_NMID, npairs, q.S + (i - 2) * (int64_t)npairs);
+    }
+  } else if (i == q.L) {
+    return;
+  } else if (blockIdx.x >= nt) {
+    const uint32_t r = blockIdx.x - nt, r0 = r * TILE_THREADS;
+    rows_projection_gf2<S>(q.U, q.W[i & 1], r0, (int)min((uint32_t)TILE_THREADS, A.nrows - r0), w, (uint32_t*)lds,
+                           q.part[i & 1] + (int64_t)r * npairs);
+  } else if (!last || q.Wlast) {
+    const int32_t* X = (const int32_t*)q.W[i & 1];
+    int32_t* Y = (int32_t*)(last ? q.Wlast : q.W[(i + 1) & 1]);
+    const Tile T = A.tiles[blockIdx.x];
+    switch (tile_kind(T.kind)) {
+      case TK_SELL: sell_tile_q<ArGF2, int32_t, int32_t, S>(A, T, X, w, Y, w, w, 1, 0); break;
+      case TK_LONG: long_tile<ArGF2, int32_t, int32_t, S, 1>(A, T, X, w, Y, w, w, 1, 0, lds); break;
+      default: stream_tile_b<ArGF2, int32_t, int32_t, S>(A, T, X, w, Y, w, w, 1, 0, lds);
+    }
   }
-  if (last) return;  // W_L only
-  // the projection reads back only rows this workgroup wrote: a workgroup barrier orders them
-  __syncthreads();
-  tile_projection_gf2(A, T, q.U, (const uint32_t*)Y, w, (uint32_t*)lds,
-                      q.part[(i + 1) & 1] + (int64_t)blockIdx.x * npairs);
 }
 
 // S_{L-1} from the folds of the last iteration.
@@ -138,7 +155,7 @@ __global__ __launch_bounds__(TILE_THREADS) void k_seq_finish_gf2(Gf2SeqArgs q) {
 }
 
 size_t gf2_sequence_part_words(const DevMat& A, int w) {
-  return 2 * ((size_t)(A.ntiles > 0 ? A.ntiles : 1) + GF2_NMID) * 32 * w * w;
+  return 2 * ((size_t)gf2_projection_blocks(A) + GF2_NMID) * 32 * w * w;
 }
 
 hipError_t launch_sequence_gf2(const DevMat& A, int64_t mte, int w, const uint32_t* U, const uint32_t* W0, int64_t L,
@@ -146,7 +163,7 @@ hipError_t launch_sequence_gf2(const DevMat& A, int64_t mte, int w, const uint32
   if (L <= 0) return hipSuccess;
   if (A.ntiles == 0) return hipErrorInvalidValue;  // every row lies in a tile, so n > 0 means tiles
   const int npairs = 32 * w * w;
-  const size_t pw = (size_t)(A.ntiles > 0 ? A.ntiles : 1) * npairs, mw = (size_t)GF2_NMID * npairs;
+  const size_t pw = (size_t)gf2_projection_blocks(A) * npairs, mw = (size_t)GF2_NMID * npairs;
   Gf2SeqArgs q;
   q.U = U;
   q.W[0] = const_cast<uint32_t*>(W0);
@@ -161,11 +178,10 @@ hipError_t launch_sequence_gf2(const DevMat& A, int64_t mte, int w, const uint32
   q.w = w;
   const int S_ = w <= 2 ? 2 : w <= 4 ? 4 : w <= 8 ? 8 : 16;  // the multi-vector tiles, as for residues
   size_t lds = tiles_lds_bytes<ArGF2>(A.max_tile_rows, mte, S_);
-  const size_t plds = gf2_projection_lds(w);
+  const size_t plds = gf2_projection_lds(w, S_);
   if (lds < plds) lds = plds;
-  hipLaunchKernelGGL(k_seq_first_gf2, dim3(A.ntiles), dim3(TILE_THREADS), plds, st, A, q);
-  const dim3 g(A.ntiles + GF2_NMID + 1), b(TILE_THREADS);
-  for (int64_t i = 0; i < L; ++i) {
+  const dim3 g(A.ntiles + gf2_projection_blocks(A) + GF2_NMID + 1), b(TILE_THREADS);
+  for (int64_t i = 0; i <= L; ++i) {
     switch (S_) {
       case 2: hipLaunchKernelGGL((k_seq_step_gf2<2>), g, b, lds, st, A, q, i); break;
       case 4: hipLaunchKernelGGL((k_seq_step_gf2<4>), g, b, lds, st, A, q, i); break;

@@ -78,3 +78,26 @@ def test_largest_tiles(dev, acc, s, m, tile_entries):
     A = synth.Csr(n, 9500, rowptr.astype(np.int64), col.astype(np.int32), np.full(rowptr[-1], m - 1, np.int64))
     A.m = m
     check(dev, A, s, torch.int32, 0, 0, 0, top=True, fixed_format="STREAM", tile_entries=tile_entries, acc=acc)
+
+
+@pytest.mark.parametrize("w", [1, 2, 3, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("n,L", [(1, 1), (255, 2), (256, 3), (513, 7)])
+@pytest.mark.parametrize("fmt", [None, "STREAM", "SELL_SORTED"])
+def test_gf2_sequence_blocks(dev, w, n, L, fmt):
+    """Packed sequences about the 256-row blocks of the projection, the first iterations (whose folds lag
+    by two) and every split of the bits over the lanes, against the product of the bit matrices."""
+    from paper_1004_3719_amd import Matrix
+    A = synth.rows(synth.spec(n, n, 17 + n, len_kind=synth.LEN_ZIPF, len_a=1, len_b=min(40, n), len_alpha=1.6,
+                              col_kind=synth.COL_UNIFORM, band_lo=-2, band_hi=2, p_pm1=0.5, val_lo=-9, val_hi=9))
+    A.m = 2
+    M = Matrix.from_synth(A, fixed_format=fmt)
+    U = torch.from_numpy(synth.vector(5, 1, n * w, -2**31, 2**31 - 1).reshape(n, w).astype(np.int32)).to(dev)
+    V = torch.from_numpy(synth.vector(5, 2, n * w, -2**31, 2**31 - 1).reshape(n, w).astype(np.int32)).to(dev)
+    S = M.sequence_gf2(U, V, L).cpu().numpy().view(np.uint32).reshape(L, 32 * w, w)
+    bits = lambda x: np.unpackbits(x.cpu().numpy().view(np.uint8).reshape(n, 4 * w), axis=1, bitorder="little").astype(np.int64)
+    u, W = bits(U), bits(V)
+    for i in range(L):
+        want = np.packbits((u.T @ W & 1).astype(np.uint8), axis=1, bitorder="little").view(np.uint32)
+        assert np.array_equal(S[i], want), i
+        W = oracle.get().spmm(A, W)
+    M.close()
