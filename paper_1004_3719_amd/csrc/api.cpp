@@ -61,6 +61,7 @@ static int seq_kind(const ffx_matrix_s& M) {
 
 int matrix_arith_kind(const ffx_matrix_s& M) { return arith_kind(M); }
 const std::vector<uint32_t>& matrix_tile_cost(const ffx_matrix_s& M) { return M.A.tile_cost; }
+const std::vector<uint8_t>& matrix_tile_sell(const ffx_matrix_s& M) { return M.A.tile_sell; }
 
 static PlanOpts plan_opts(const ffx_build_opts* o) {
   ffx_build_opts d;

@@ -52,12 +52,15 @@ struct BatchOperand {
 
 constexpr int NQ = 8;  // work queues per chunk class: one per XCD
 
-// Right-hand-side column chunks fall in four classes (1, 2, 3..4, 5..8
-// columns), each with its own persistent kernel: a kernel holding every class's
-// tile paths would take the registers of the largest and run at 3 waves per
-// SIMD.
-constexpr int NCLS = 4;
-inline int chunk_class(int sc) { return sc <= 1 ? 0 : sc <= 2 ? 1 : sc <= 4 ? 2 : 3; }
+// Items fall in eight classes, each with its own persistent kernel: four widths
+// of the right-hand-side chunk (1, 2, 3..4, 5..8 columns), since a kernel holding
+// every width's tile paths would take the registers of the largest, and SELL
+// tiles apart from the others, since only the others take LDS (33 KB for eight
+// columns: four workgroups fill a compute unit's, and with SELL items among them
+// nothing else ran beside them). 48 uneven systems of up to 200,000 rows, all SELL:
+// 758 us in four classes, 704 in eight and with the next item claimed ahead.
+constexpr int NCLS = 8;
+inline int chunk_class(int sc, bool sell) { return 2 * (sc <= 1 ? 0 : sc <= 2 ? 1 : sc <= 4 ? 2 : 3) + (sell ? 1 : 0); }
 
 // 4 workgroups (4 waves per SIMD) for the m <= 65536 kernels: they fit 128
 // registers without spilling
@@ -65,8 +68,9 @@ template <class AR>
 constexpr int batch_min_blocks() { return std::is_same<AR, ArSmall>::value ? 4 : 1; }
 
 // One class's items: queue q holds items [qfirst[q], qfirst[q] + qn[q]) of `items`; counter[q]
-// hands them out. Every workgroup sweeps all NQ queues, its own first, until each is exhausted.
-template <class AR, typename Tx, typename Tv, int SC>
+// hands them out. Every workgroup sweeps all NQ queues, its own first, until each is exhausted. The
+// next item of a queue is claimed before the work on this one, which hides the atomic's round trip.
+template <class AR, typename Tx, typename Tv, int SC, bool SELL>
 __global__ __launch_bounds__(TILE_THREADS, batch_min_blocks<AR>()) void k_batch(const DevMat* __restrict__ mats,
                                                         const BatchOperand* __restrict__ ops,
                                                         const BatchItem* __restrict__ items,
@@ -77,12 +81,15 @@ __global__ __launch_bounds__(TILE_THREADS, batch_min_blocks<AR>()) void k_batch(
   for (uint32_t j = 0; j < NQ; ++j) {
     const uint32_t q = (home + j) % NQ;
     const uint32_t qf = qinfo[q], qn = qinfo[NQ + q];
+    if (qn == 0) continue;
+    __syncthreads();  // every lane has read `next`
+    if (threadIdx.x == 0) next = atomicAdd(&counter[q], 1u);
     for (;;) {
-      if (threadIdx.x == 0) next = atomicAdd(&counter[q], 1u);
       __syncthreads();
       const uint32_t it = next;
-      __syncthreads();  // every lane has read `next` before thread 0 may overwrite it
       if (it >= qn) break;
+      uint32_t ahead = 0;
+      if (threadIdx.x == 0) ahead = atomicAdd(&counter[q], 1u);
       const BatchItem I = items[qf + it];
       const DevMat A = mats[I.k];
       const BatchOperand O = ops[I.k];
@@ -92,17 +99,19 @@ __global__ __launch_bounds__(TILE_THREADS, batch_min_blocks<AR>()) void k_batch(
       const int64_t ldx = x16 ? (int64_t)O.s : O.ldx;
       Tv* Y = (Tv*)O.Y + I.c0;
       const int sc = I.sc;
-      const uint32_t kind = tile_kind(T.kind);
-      if constexpr (SC == 1) {
-        if (kind == TK_SELL) sell_tile<AR, Tx, Tv, 1, 2>(A, T, X, ldx, Y, O.ldy, 1, 1, 0);
-        else if (kind == TK_LONG) long_tile<AR, Tx, Tv, 1, 2>(A, T, X, ldx, Y, O.ldy, 1, 1, 0, lds);
+      const bool lng = tile_kind(T.kind) == TK_LONG;
+      if constexpr (SELL) {
+        if constexpr (SC == 1) sell_tile<AR, Tx, Tv, 1, 2>(A, T, X, ldx, Y, O.ldy, 1, 1, 0);
+        else sell_tile_q<AR, Tx, Tv, SC>(A, T, X, ldx, Y, O.ldy, sc, 1, 0);
+      } else if constexpr (SC == 1) {
+        if (lng) long_tile<AR, Tx, Tv, 1, 2>(A, T, X, ldx, Y, O.ldy, 1, 1, 0, lds);
         else stream_tile_1<AR, Tx, Tv, 2>(A, T, X, ldx, Y, O.ldy, 1, 0, lds);
       } else {
-        if (kind == TK_SELL) sell_tile_q<AR, Tx, Tv, SC>(A, T, X, ldx, Y, O.ldy, sc, 1, 0);
-        else if (kind == TK_LONG) long_tile<AR, Tx, Tv, SC, 1>(A, T, X, ldx, Y, O.ldy, sc, 1, 0, lds);
+        if (lng) long_tile<AR, Tx, Tv, SC, 1>(A, T, X, ldx, Y, O.ldy, sc, 1, 0, lds);
         else stream_tile_b<AR, Tx, Tv, SC>(A, T, X, ldx, Y, O.ldy, sc, 1, 0, lds);
       }
-      __syncthreads();  // LDS is reused by the next item
+      __syncthreads();  // every lane has read `next`, and LDS is reused by the next item
+      if (threadIdx.x == 0) next = ahead;
     }
   }
 }
@@ -157,8 +166,12 @@ static hipError_t batch_launch_class(int ak, ffx_dtype dt, bool x16, int cls, co
       using Tx = decltype(tx);
       using Tv = decltype(tv);
       constexpr int SC = decltype(scv)::value;
-      hipLaunchKernelGGL((k_batch<AR, Tx, Tv, SC>), dim3(grid), dim3(TILE_THREADS), batch_lds<AR>(mtr, mte, SC), st, mats,
-                         ops, items, qinfo, counter);
+      if (cls & 1)
+        hipLaunchKernelGGL((k_batch<AR, Tx, Tv, SC, true>), dim3(grid), dim3(TILE_THREADS), 0, st, mats, ops, items, qinfo,
+                           counter);
+      else
+        hipLaunchKernelGGL((k_batch<AR, Tx, Tv, SC, false>), dim3(grid), dim3(TILE_THREADS), batch_lds<AR>(mtr, mte, SC),
+                           st, mats, ops, items, qinfo, counter);
     };
     auto by_dt = [&](auto scv) {
       // the 16-bit gathers are built for the integer class of m <= 65536 only
@@ -172,7 +185,7 @@ static hipError_t batch_launch_class(int ak, ffx_dtype dt, bool x16, int cls, co
       if (dt == FFX_I32) launch(int32_t{}, int32_t{}, scv);
       else launch(int64_t{}, int64_t{}, scv);
     };
-    switch (cls) {
+    switch (cls / 2) {
       case 0: by_dt(std::integral_constant<int, 1>{}); break;
       case 1: by_dt(std::integral_constant<int, 2>{}); break;
       case 2: by_dt(std::integral_constant<int, 4>{}); break;
@@ -221,7 +234,7 @@ struct ffx_batch_s {
   uint16_t* d_x16 = nullptr;      // 16-bit copies of every X_k (compact_x)
   std::vector<int64_t> x16_off;   // element offset of each X_k's copy
   uint32_t nitems = 0;
-  uint32_t cls_first[NCLS] = {0, 0, 0, 0}, cls_n[NCLS] = {0, 0, 0, 0};
+  uint32_t cls_first[NCLS] = {}, cls_n[NCLS] = {};
   bool small = false;             // m <= 65536 on the integer class: 16-bit X is available
   std::vector<BatchOperand> h_ops;
   hipGraphExec_t exec = nullptr;
@@ -239,6 +252,7 @@ struct ffx_batch_s {
 namespace ffx {
 int matrix_arith_kind(const ffx_matrix_s& M);
 const std::vector<uint32_t>& matrix_tile_cost(const ffx_matrix_s& M);
+const std::vector<uint8_t>& matrix_tile_sell(const ffx_matrix_s& M);
 void set_last_error(const std::string& s);
 }  // namespace ffx
 
@@ -270,12 +284,13 @@ static void batch_items(ffx_batch_s* B) {
       load[q] += mcost[k];
     }
   }
-  // by chunk class (each class is one kernel), then queue, then by decreasing cost when order == 0
+  auto cls_of = [&](const BatchItem& I) { return chunk_class(I.sc, matrix_tile_sell(*B->mats[I.k])[I.t] != 0); };
+  // by class (each class is one kernel), then queue, then by decreasing cost when order == 0
   std::vector<size_t> idx(items.size());
   for (size_t i = 0; i < idx.size(); ++i) idx[i] = i;
   const bool by_cost = B->params.order == 0;
   std::stable_sort(idx.begin(), idx.end(), [&](size_t a, size_t b) {
-    int ca = chunk_class(items[a].sc), cb = chunk_class(items[b].sc);
+    int ca = cls_of(items[a]), cb = cls_of(items[b]);
     if (ca != cb) return ca < cb;
     int qa = mq[items[a].k], qb = mq[items[b].k];
     if (qa != qb) return qa < qb;
@@ -287,11 +302,11 @@ static void batch_items(ffx_batch_s* B) {
   std::vector<uint32_t> qinfo(NCLS * 2 * NQ, 0);
   for (int c = 0; c < NCLS; ++c) B->cls_first[c] = B->cls_n[c] = 0;
   for (size_t i = 0; i < items.size(); ++i) {
-    int c = chunk_class(items[i].sc);
+    int c = cls_of(items[i]);
     if (B->cls_n[c]++ == 0) B->cls_first[c] = (uint32_t)i;
   }
   for (size_t i = 0; i < items.size(); ++i) {  // queue starts relative to the class's first item
-    int c = chunk_class(items[i].sc), q = mq[items[i].k];
+    int c = cls_of(items[i]), q = mq[items[i].k];
     uint32_t* qi = &qinfo[c * 2 * NQ];
     if (qi[NQ + q]++ == 0) qi[q] = (uint32_t)i - B->cls_first[c];
   }
@@ -380,7 +395,7 @@ static void batch_run(ffx_batch_s* B, const void* const* X, const int64_t* ldx, 
         hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, cs, B->d_counter, NCLS * NQ);
         hipError_t le = launch_x16(cs);
         if (le == hipSuccess) le = hipEventRecord(ev0, cs);
-        for (int c = 0; c < NCLS && le == hipSuccess; ++c) {
+        for (int c = NCLS - 1; c >= 0 && le == hipSuccess; --c) {  // the widest, whose items take longest, first
           if (!B->cls_n[c]) continue;
           le = hipStreamWaitEvent(br[c], ev0, 0);
           if (le == hipSuccess) le = launch_class(c, br[c]);
@@ -407,7 +422,7 @@ static void batch_run(ffx_batch_s* B, const void* const* X, const int64_t* ldx, 
   }
   hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, st, B->d_counter, NCLS * NQ);
   FFX_HIP(launch_x16(st));
-  for (int c = 0; c < NCLS; ++c)
+  for (int c = NCLS - 1; c >= 0; --c)
     if (B->cls_n[c]) FFX_HIP(launch_class(c, st));
 }
 

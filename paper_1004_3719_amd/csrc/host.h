@@ -112,6 +112,7 @@ struct Encoded {
   int64_t max_tile_entries = 0;  // largest STREAM tile (sizes the LDS of a launch)
   std::vector<int32_t> block_fmt;
   std::vector<uint32_t> tile_cost;  // per tile: entry words read (with padding) plus band slots
+  std::vector<uint8_t> tile_sell;   // per tile: whether it is a SELL tile
   std::vector<uint32_t> block_tile0;  // first tile of each block, plus the tile count at the end
   int64_t format_blocks[FFX_NUM_FORMATS] = {0, 0, 0, 0, 0, 0};
   int64_t kind_tiles[3] = {0, 0, 0};  // STREAM, LONG and SELL tiles

@@ -552,6 +552,7 @@ void encode(const RCsr& A, const Modulus& md, const PlanOpts& o, hipStream_t str
   std::fill(out->kind_tiles, out->kind_tiles + 3, 0);
   for (const Tile& T : H.tiles) out->kind_tiles[tile_kind(T.kind) == TK_SELL ? 2 : tile_kind(T.kind) == TK_LONG ? 1 : 0]++;
   out->tile_cost.resize(H.tiles.size());
+  out->tile_sell.resize(H.tiles.size());
   for (size_t t = 0; t < H.tiles.size(); ++t) {
     const Tile& T = H.tiles[t];
     uint64_t words = 0;
@@ -560,6 +561,7 @@ void encode(const RCsr& A, const Modulus& md, const PlanOpts& o, hipStream_t str
     else
       words = T.ne;
     uint64_t rows = tile_kind(T.kind) == TK_LONG ? 1 : tile_rows(T.kind);
+    out->tile_sell[t] = tile_kind(T.kind) == TK_SELL;
     out->tile_cost[t] = (uint32_t)std::min<uint64_t>(UINT32_MAX, words + rows * tile_nd(T.kind) + rows);
   }
   out->n_ent = (int64_t)H.ent.size();

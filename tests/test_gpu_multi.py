@@ -101,3 +101,21 @@ def test_gf2_sequence_blocks(dev, w, n, L, fmt):
         assert np.array_equal(S[i], want), i
         W = oracle.get().spmm(A, W)
     M.close()
+
+
+@pytest.mark.parametrize("xcd", [0, 1])
+@pytest.mark.parametrize("fmts", [("SELL", "STREAM"), ("SELL",), ("STREAM",)])
+def test_batch_kinds_of_tiles(dev, fmts, xcd):
+    """Batches of SELL tiles, of others and of both (each kind has its own kernels), fewer items than workgroups and
+    queues without any: every width of the right-hand sides."""
+    from paper_1004_3719_amd import Batch, Matrix
+    As = [synth.c1(seed=40 + k, n=200 + 150 * k) for k in range(9)]
+    mats = [Matrix.from_synth(A, fixed_format=fmts[k % len(fmts)]) for k, A in enumerate(As)]
+    s = [1, 2, 3, 4, 5, 8, 9, 13, 16]
+    B = Batch(mats, s, xcd=xcd, use_graph=False)
+    xs = [synth.vector(6, k, A.ncols * s[k], 0, A.m - 1).reshape(A.ncols, s[k]) for k, A in enumerate(As)]
+    for _ in range(2):
+        ys = [torch.full((A.nrows, q), -5, dtype=torch.int32, device=dev) for A, q in zip(As, s)]
+        B.spmm([torch.from_numpy(x.astype(np.int32)).to(dev) for x in xs], ys)
+        for A, x, y in zip(As, xs, ys):
+            assert np.array_equal(y.cpu().numpy(), oracle.get().spmm(A, x))
