@@ -98,6 +98,7 @@ hipError_t launch_sequence(int ak, bool only_sell, const DevMat& A, int64_t mte,
 // (0 for the binned form: this product has none).
 struct TransposeInfo {
   int64_t nnz;      // stored entries
+  int64_t nband;    // of them in diagonals
   int64_t nrec;     // records of all batches
   uint32_t nbatch;  // batches (DevMat::tbatch), 0 when there are none
 };

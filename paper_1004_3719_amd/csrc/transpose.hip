@@ -418,9 +418,15 @@ static int pow2_at_least(int s) { return s <= 1 ? 1 : s <= 2 ? 2 : s <= 4 ? 4 : 
 //    them where the outputs allow, so that panels and parts fill 256 compute
 //    units with few parts to add up. More than TB_MAXP panels would leave a
 //    batch only a few records per panel: scattered.
-//  - Small products: the binned form's three kernels take at least 38 us, the
-//    scattered form's 14 us and 43 ps per transaction, so they meet at about
-//    2^19 transactions (270,000 entries, one vector: 27 us against 43).
+//  - Small products: the binned form's three kernels take about 35 us a call, as
+//    does a scatter of 2^13 transactions; with more, few output rows take many
+//    atomics each, and those to one address wait for one another (3,000 rows of
+//    30 entries, 8 vectors: 34 us against 118; 5,068 rows of about 26, one
+//    vector: 41 against 76; 1,000 rows of 10, one vector: 32 and 35).
+//  - Large products of one vector and almost only diagonals: adjacent lanes add to
+//    adjacent sums, so eight terms are one transaction and the scatter is cheaper
+//    than records (211,991 rows, 55 diagonals: 82 us against 110). Below 2^22 entries
+//    the records win there too (50,083 rows of 21: 38 us against 44).
 //  - Scratch: the records of all entries, at most TB_MAX_SCRATCH.
 struct TPlan {
   bool ok = false;
@@ -428,7 +434,8 @@ struct TPlan {
   size_t rec_bytes = 0, off_bytes = 0, part_bytes = 0;
 };
 constexpr size_t TB_MAX_SCRATCH = (size_t)1 << 30;
-constexpr int64_t T_MIN_TRANSACTIONS = (int64_t)1 << 19;
+constexpr int64_t T_MIN_TRANSACTIONS = (int64_t)1 << 13;
+constexpr int64_t T_MIN_BAND = (int64_t)1 << 22;
 
 static TPlan t_plan(const DevMat& A, const TransposeInfo& I, int s) {
   TPlan t;
@@ -436,6 +443,7 @@ static TPlan t_plan(const DevMat& A, const TransposeInfo& I, int s) {
   const int64_t n = A.ncols;
   const int64_t transactions = I.nnz * ((s + 7) / 8);
   if (!I.nbatch || transactions < T_MIN_TRANSACTIONS) return t;
+  if (s == 1 && I.nnz >= T_MIN_BAND && I.nnz - I.nband + I.nband / 8 < I.nnz / 5) return t;
   uint32_t top = 14;
   for (int k = 1; k < sp; k *= 2) --top;
   t.sh = 6;

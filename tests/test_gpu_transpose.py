@@ -124,3 +124,25 @@ def test_column_sorted_largest_sums(dev, m):
 
 def test_column_sorted_reordered(dev):
     check(dev, powerlaw(40_000, 40_000, 32749), 1, col_sorted=1, reorder=True)
+
+
+@pytest.mark.parametrize("m", [2, 65521, M31])
+@pytest.mark.parametrize("s", [1, 2, 5, 8, 9, 16])
+@pytest.mark.parametrize("fmt", ["STREAM", "SELL_SORTED", "BAND_STREAM", "BAND_SELL"])
+def test_scattered_small(dev, m, s, fmt):
+    """Below the fewest transactions that are binned: the atomics of one entry side by side."""
+    A = powerlaw(201, 190, m, seed=23)
+    assert A.nnz * ((s + 7) // 8) < 1 << 13
+    check(dev, A, s, fixed_format=fmt)
+
+
+def test_scattered_band(dev):
+    """Almost only diagonals, one vector, more than 2^22 entries: atomics of adjacent lanes on adjacent sums."""
+    n, w = 90_001, 48
+    row = np.repeat(np.arange(n), w)
+    col = (row + np.tile(np.arange(-20, w - 20), n)) % n
+    rng = np.random.default_rng(3)
+    rowptr = np.arange(0, n * w + 1, w, dtype=np.int64)
+    A = synth.Csr(n, n, rowptr, col.astype(np.int32), rng.integers(2, M31 - 1, n * w))
+    A.m = M31
+    check(dev, A, 1, fixed_format="BAND_SELL")
