@@ -124,8 +124,8 @@ typedef struct {
                                matrices. */
   int32_t col_sorted;       /* m <= 65536 with the int64 accumulator: 1 = also store A as column-sorted
                                row groups (about one per compute unit, entries sorted by column inside
-                               a group) that ffx_spmv and ffx_spmv_noalloc use for y = alpha*A*x +
-                               beta*y: the lanes of one gather then share cache lines of x. Costs a
+                               a group) that ffx_spmv, ffx_spmv_noalloc, ffx_spmv_t and one-vector
+                               ffx_power use: the lanes of one gather then share cache lines of x. Costs a
                                second copy of A on the device. 0 = never; -1 (default) = when A has
                                at least 4 Mi entries and 256 Ki columns. Never changes a result. */
 } ffx_build_opts;
@@ -224,8 +224,10 @@ ffx_status ffx_spmv(ffx_matrix A, uint32_t alpha, const void* x, uint32_t beta, 
                     void* stream);
 
 /* y <- alpha*A^T*x + beta*y (mod m). x: nrows entries, y: ncols entries.
- * Uses the stored A^T when the handle has one, else a scatter with 64-bit
- * integer atomics into a temporary, which is exact in any order. */
+ * Uses the stored A^T when the handle has one, else the column-sorted groups
+ * when it has those, else records of A's entries binned by output rows in a
+ * temporary of at most 1 GiB, or a scatter with 64-bit integer atomics where
+ * that would not pay or cannot be had: all exact, in any order. */
 ffx_status ffx_spmv_t(ffx_matrix A, uint32_t alpha, const void* x, uint32_t beta, void* y, ffx_dtype dtype,
                       void* stream);
 
