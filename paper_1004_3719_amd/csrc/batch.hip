@@ -357,7 +357,9 @@ static void batch_run(ffx_batch_s* B, const void* const* X, const int64_t* ldx, 
   }
   for (int k = 0; k < B->count; ++k) {
     BatchOperand& o = B->h_ops[k];
-    o.X16 = x16 ? B->d_x16 + B->x16_off[k] : nullptr;
+    const DevMat& A = B->mats[k]->A.dm;
+    o.X = readable_x(A, o.X);
+    o.X16 = x16 ? (uint16_t*)readable_x(A, B->d_x16 + B->x16_off[k]) : nullptr;  // without columns nothing is copied there
     o.ncols = B->mats[k]->info.ncols;
     o.s = B->s[k];
   }

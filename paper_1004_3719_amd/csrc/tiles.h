@@ -1109,6 +1109,11 @@ hipError_t raise_tiles_lds(int S) {
   }
 }
 
+// What the tiles read as X. A one-vector tile's padding gathers element 0 with the value 0, and a matrix without
+// columns has tiles (its rows are all padding) but no such element: X is empty and may be null, so the tile table
+// stands in for it.
+inline const void* readable_x(const DevMat& A, const void* X) { return A.ncols ? X : (const void*)A.tiles; }
+
 // x16: when not null, a 16-bit copy of the one vector (s must be 1)
 template <class AR, typename Tv>
 hipError_t launch_tiles_t(const DevMat& A, int64_t max_tile_entries, const void* X, int64_t ldx, void* Y, int64_t ldy,
@@ -1122,7 +1127,7 @@ hipError_t launch_tiles_t(const DevMat& A, int64_t max_tile_entries, const void*
     if (e != hipSuccess) return e;
   }
   dim3 grid(nblocks ? nblocks : A.ntiles), block(TILE_THREADS);
-  const Tv* x = (const Tv*)X;
+  const Tv* x = (const Tv*)readable_x(A, X);
   Tv* y = (Tv*)Y;
   if (S == 1) {
     const int U = unroll_for(max_tile_entries);
