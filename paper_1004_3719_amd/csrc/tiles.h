@@ -980,10 +980,19 @@ __device__ inline void stream_tile_m(const DevMat& A, const Tile& T, const Tx* _
 #pragma unroll
       for (int e = 0; e < EU; ++e) {
         if (p + e >= p1) break;
-        while (p + e >= next) {
+        if (p + e >= next) {
           flush();
           acc.init(A);
           next = rps[++r + 1];
+          if (p + e >= next) {  // past rows without entries by bisection: a walk over them is a chain of LDS reads
+            uint32_t hi = nr;
+            while (hi - r > 1) {
+              const uint32_t mid = (r + hi) >> 1;
+              if (rps[mid] <= p + e) r = mid;
+              else hi = mid;
+            }
+            next = rps[r + 1];
+          }
         }
 #pragma unroll
         for (int c = 0; c < C; ++c) acc.a[c] += mul_term<AR>(v[e], xv[e][c], A.m);
