@@ -38,12 +38,15 @@ def lengths(kind, n):
         lens[at] = np.arange(len(at)) % 9 + 1
     elif kind == "long":  # rows of several runs between empty ones
         lens[100::300] = 1500
+    elif kind == "groups":  # tiles of as many entries as groups of lanes, one fewer and one more
+        for k, ne in enumerate((63, 64, 65, 127, 128, 129, 255, 256, 257)):
+            lens[256 * k + 3], lens[256 * k + 200] = ne // 2, ne - ne // 2
     elif kind == "every":
         lens[::50] = 1
     return lens
 
 
-@pytest.mark.parametrize("kind", ["ends", "gaps", "long", "every", "none"])
+@pytest.mark.parametrize("kind", ["ends", "gaps", "long", "groups", "every", "none"])
 @pytest.mark.parametrize("m,acc", [(2, "auto"), (65521, "auto"), (M31, "auto"), (2039, "fp32"), (1_000_003, "fp64c")])
 def test_mostly_empty_rows(dev, kind, m, acc):
     from paper_1004_3719_amd import Matrix
