@@ -78,16 +78,20 @@ __device__ inline void load_chunk(const DevMat& A, const Tile& T, uint32_t ch, u
 #pragma unroll
     for (int k = 0; k < WIDE; ++k) slot[k] = 0;
   } else {
+    // the last row whose start is <= e + k, by bisection also from one entry to the next: a walk over empty rows
+    // is a chain of LDS reads (a band with a few entries beside it: 25 us for 255 rows)
     const uint32_t nr = tile_rows(T.kind);
-    uint32_t lo = 0, hi = nr;  // last row whose start is <= e
-    while (hi - lo > 1) {
-      const uint32_t mid = (lo + hi) >> 1;
-      if (rps[mid] <= e) lo = mid;
-      else hi = mid;
-    }
+    uint32_t lo = 0;
 #pragma unroll
     for (int k = 0; k < WIDE; ++k) {
-      while (lo + 1 < nr && rps[lo + 1] <= e + k) ++lo;
+      if (e + k < T.ne && (k == 0 || (lo + 1 < nr && rps[lo + 1] <= e + k))) {
+        uint32_t hi = nr;
+        while (hi - lo > 1) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (rps[mid] <= e + k) lo = mid;
+          else hi = mid;
+        }
+      }
       slot[k] = lo;
     }
   }
@@ -141,16 +145,23 @@ __global__ __launch_bounds__(TILE_THREADS) void k_scatter_t(DevMat A, const Tv* 
       }
     }
   }
-  // band part: SP lanes per (diagonal, row)
+  // band part: SP lanes per row, whose x stays in a register, and the values of DB diagonals in flight together
+  constexpr uint32_t DB = 8;
   const uint32_t nd = tile_nd(T.kind), rows = tile_rows(T.kind);
-  for (uint32_t q = tid / SP; q < rows * nd; q += TILE_THREADS / SP) {
-    const uint32_t d = q / rows, slot = q % rows;
+  for (uint32_t slot = tid / SP; nd && slot < rows; slot += TILE_THREADS / SP) {
     const uint32_t row = slot_row(A, T, slot);
-    const uint32_t v = ldval<TVal<K>>(A.bval, T.b0 + d * rows + slot);
-    if (!v || row >= A.nrows || (int)comp >= s) continue;
-    const int64_t col = (int64_t)row + A.boffs[T.boff + d];
-    const uint32_t t = tterm<K>(v, (uint32_t)X[(int64_t)row * ldx + comp], A);
-    atomicAdd(&acc[col * SP + comp], (unsigned long long)t);
+    if (row >= A.nrows || (int)comp >= s) continue;
+    const uint32_t x = (uint32_t)X[(int64_t)row * ldx + comp];
+    for (uint32_t d0 = 0; d0 < nd; d0 += DB) {
+      uint32_t v[DB];
+#pragma unroll
+      for (uint32_t d = 0; d < DB; ++d)
+        v[d] = d0 + d < nd ? ldval<TVal<K>>(A.bval, T.b0 + (d0 + d) * rows + slot) : 0u;
+#pragma unroll
+      for (uint32_t d = 0; d < DB; ++d)
+        if (v[d])  // an absent entry may lie outside the matrix
+          atomicAdd(&acc[((int64_t)row + A.boffs[T.boff + d0 + d]) * SP + comp], (unsigned long long)tterm<K>(v[d], x, A));
+    }
   }
 }
 

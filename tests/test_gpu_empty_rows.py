@@ -40,7 +40,8 @@ def lengths(kind, n):
         lens[100::300] = 1500
     elif kind == "groups":  # tiles of as many entries as groups of lanes, one fewer and one more
         for k, ne in enumerate((63, 64, 65, 127, 128, 129, 255, 256, 257)):
-            lens[256 * k + 3], lens[256 * k + 200] = ne // 2, ne - ne // 2
+            if 256 * k + 200 < n:
+                lens[256 * k + 3], lens[256 * k + 200] = ne // 2, ne - ne // 2
     elif kind == "every":
         lens[::50] = 1
     return lens
@@ -59,6 +60,33 @@ def test_mostly_empty_rows(dev, kind, m, acc):
             got = M.spmm(torch.from_numpy(X).to(dtype).to(dev))
             assert np.array_equal(got.cpu().numpy(), oracle.get().spmm(A, X)), (s, dtype)
     M.close()
+
+
+@pytest.mark.parametrize("kind", ["ends", "gaps", "long", "groups", "every", "none"])
+@pytest.mark.parametrize("n,diagonals", [(700, 0), (5000, 0), (700, 3), (5000, 3), (5000, 20)])
+@pytest.mark.parametrize("m", [2, 65521, 1_000_003, M31])
+def test_transposed_mostly_empty_rows(dev, kind, n, diagonals, m):
+    """Without a stored transpose, below and above the line between atomics and records: entries that come after
+    stretches of empty rows, alone and beside diagonals (a band from the first to the last column: entries outside)."""
+    from paper_1004_3719_amd import Matrix
+    print("[case] transposed empty rows", kind, n, diagonals, m, flush=True)
+    A = matrix(lengths(kind, n), n, m)
+    if diagonals:
+        row, val = np.repeat(np.arange(n), diagonals), np.random.default_rng(4).integers(0, m, n * diagonals)
+        col = row + np.tile(np.arange(diagonals) - 1, n)
+        ok = (col >= 0) & (col < n)
+        row = np.concatenate([np.repeat(np.arange(n), np.diff(A.rowptr)), row[ok]])
+        col, val = np.concatenate([A.col, col[ok]]), np.concatenate([A.val, val[ok]])
+        at = np.argsort(row, kind="stable")
+        rp = np.concatenate([[0], np.cumsum(np.bincount(row, minlength=n))]).astype(np.int64)
+        A = synth.Csr(n, n, rp, col[at].astype(np.int32), val[at], m=m)
+    for fmt in ("STREAM", "BAND_STREAM", "BAND_SELL"):
+        M = Matrix.from_synth(A, fixed_format=fmt)
+        for s in (1, 2, 3, 8, 16):
+            X = synth.vector(8, s, n * s, 0, m - 1).reshape(n, s)
+            got = M.spmm_t(torch.from_numpy(X).to(dev))
+            assert np.array_equal(got.cpu().numpy(), oracle.get().spmm_t(A, X)), (fmt, s)
+        M.close()
 
 
 @pytest.mark.parametrize("s", [2, 4, 8])
