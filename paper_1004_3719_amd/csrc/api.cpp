@@ -450,7 +450,7 @@ static void product(ffx_matrix M, bool trans, int s, uint32_t alpha, const void*
       if (sg_bytes) (void)hipGetLastError();
     }
     const Encoded& E = M->A;
-    const TransposeInfo I{E.nnz, E.n_band, E.t_recs, E.t_batches};
+    const TransposeInfo I{E.nnz, E.n_band, E.t_recs, E.t_batches, E.t_runs};
     void* tmp = nullptr;
     size_t bytes = transpose_scratch_bytes(E.dm, I, s, true);
     const bool binned = bytes && hipMallocAsync(&tmp, bytes, st) == hipSuccess;

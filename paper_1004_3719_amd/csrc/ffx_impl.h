@@ -72,6 +72,7 @@ struct TBatch {
   uint32_t tile, first, n, rec0;
 };
 static_assert(sizeof(TBatch) == 16, "batch layout");
+constexpr int T_SHIFTS = 15;  // its panels have 2^6 to 2^14 output rows
 
 // Everything a kernel needs about one encoded matrix (passed by value).
 struct DevMat {

@@ -109,6 +109,7 @@ struct Encoded {
   int64_t device_bytes = 0, stream_bytes = 0;
   int64_t t_recs = 0;            // transposed product: records of all batches
   uint32_t t_batches = 0;        // and the number of batches (0: more records than 32 bits index)
+  int64_t t_runs[T_SHIFTS] = {};  // and their runs of records by panel (TransposeInfo)
   int64_t max_tile_entries = 0;  // largest STREAM tile (sizes the LDS of a launch)
   std::vector<int32_t> block_fmt;
   std::vector<uint32_t> tile_cost;  // per tile: entry words read (with padding) plus band slots

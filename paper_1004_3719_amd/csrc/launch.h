@@ -101,6 +101,7 @@ struct TransposeInfo {
   int64_t nband;    // of them in diagonals
   int64_t nrec;     // records of all batches
   uint32_t nbatch;  // batches (DevMat::tbatch), 0 when there are none
+  const int64_t* runs;  // [T_SHIFTS]: about how many runs of records of one panel the batches hold, for panels of 2^sh rows
 };
 size_t transpose_scratch_bytes(const DevMat& A, const TransposeInfo& I, int s, bool binned);
 hipError_t launch_transpose(const DevMat& A, const TransposeInfo& I, ffx_dtype dt, const void* X, int64_t ldx, void* Y,

@@ -485,6 +485,40 @@ void encode(const RCsr& A, const Modulus& md, const PlanOpts& o, hipStream_t str
     }
   }
   if (nrec >= UINT32_MAX) tbatch.clear();
+  // The batches' runs, from the range of columns of each: at most one run to a panel in that range, or to a record
+  std::vector<int64_t> runs(T_SHIFTS, 0);
+#pragma omp parallel
+  {
+    int64_t mine[T_SHIFTS] = {};
+#pragma omp for schedule(static)
+    for (int64_t b = 0; b < (int64_t)tbatch.size(); ++b) {
+      const TBatch& B = tbatch[b];
+      const Tile& T = H.tiles[B.tile];
+      int64_t lo = INT64_MAX, hi = -1, n = 0;
+      if (B.n & TB_BAND) {  // about its rows' diagonals
+        const int64_t nd = B.n & ~TB_BAND, r0 = tile_kind(T.kind) == TK_SELL && (T.kind & TF_SORTED) ? H.perm[T.row0] : T.row0;
+        n = nd * tile_rows(T.kind);
+        lo = r0 + H.boffs[T.boff + B.first];
+        hi = r0 + tile_rows(T.kind) + H.boffs[T.boff + B.first + nd - 1];
+      } else {
+        const uint32_t* w = &H.ent[T.e0 + (size_t)B.first * WCHUNK];
+        const size_t words = tile_kind(T.kind) == TK_SELL ? (size_t)B.n * WCHUNK
+                                                         : std::min<size_t>((size_t)B.n * WCHUNK, T.ne - (size_t)B.first * WCHUNK);
+        for (size_t k = 0; k < words; ++k) {
+          if ((w[k] >> TAG_SHIFT) == TAG_PAD) continue;
+          const int64_t c = w[k] & COL_MASK;
+          lo = std::min(lo, c);
+          hi = std::max(hi, c);
+          ++n;
+        }
+      }
+      if (n)
+        for (int sh = 0; sh < T_SHIFTS; ++sh) mine[sh] += std::min(n, (hi >> sh) - (lo >> sh) + 1);
+    }
+#pragma omp critical
+    for (int sh = 0; sh < T_SHIFTS; ++sh) runs[sh] += mine[sh];
+  }
+  std::copy(runs.begin(), runs.end(), out->t_runs);
   add_part<TBatch>(offs, total, tbatch.size());
   if (total == 0) total = 256;
   std::vector<unsigned char> host(total, 0);

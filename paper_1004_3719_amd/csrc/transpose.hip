@@ -133,15 +133,40 @@ __global__ __launch_bounds__(TILE_THREADS) void k_scatter_t(DevMat A, const Tv* 
 #pragma unroll
     for (int k = 0; k < WIDE; ++k) {
       const uint32_t row = slot_row(A, T, slot[k]);
-#pragma unroll
-      for (int p = 0; p < SP; ++p) {
+      auto pass = [&](int p, uint32_t& wp, uint32_t& vp, uint32_t& rp) {  // entry, value and row of pass p
         const int src = p * (WAVE / SP) + (int)sub;
-        const uint32_t wp = SP == 1 ? w[k] : (uint32_t)__shfl((int)w[k], src);
-        const uint32_t vp = SP == 1 ? v[k] : (uint32_t)__shfl((int)v[k], src);
-        const uint32_t rp = SP == 1 ? row : (uint32_t)__shfl((int)row, src);
-        if ((wp >> TAG_SHIFT) == TAG_PAD || rp >= A.nrows || (int)comp >= s) continue;
-        const uint32_t t = tterm<K>(tvalue(wp, vp, A.m), (uint32_t)X[(int64_t)rp * ldx + comp], A);
+        wp = SP == 1 ? w[k] : (uint32_t)__shfl((int)w[k], src);
+        vp = SP == 1 ? v[k] : (uint32_t)__shfl((int)v[k], src);
+        rp = SP == 1 ? row : (uint32_t)__shfl((int)row, src);
+        return (wp >> TAG_SHIFT) != TAG_PAD && rp < A.nrows && (int)comp < s;
+      };
+      auto term = [&](uint32_t wp, uint32_t vp, uint32_t rp) {
+        return tterm<K>(tvalue(wp, vp, A.m), (uint32_t)X[(int64_t)rp * ldx + comp], A);
+      };
+      auto add = [&](uint32_t wp, uint32_t t) {
         atomicAdd(&acc[(int64_t)(wp & COL_MASK) * SP + comp], (unsigned long long)t);
+      };
+      if constexpr (SP <= 4) {
+        // every pass's load of x before the first atomic, which would keep it behind (300 rows of 10, 3 vectors: 27 us,
+        // now 21); with 16 lanes to an entry that is slower (1,000,000 rows with three entries in every tenth, 12
+        // vectors: 139 us and 107)
+        uint32_t wp[SP], t[SP];
+        bool on[SP];
+#pragma unroll
+        for (int p = 0; p < SP; ++p) {
+          uint32_t vp, rp;
+          on[p] = pass(p, wp[p], vp, rp);
+          t[p] = on[p] ? term(wp[p], vp, rp) : 0u;
+        }
+#pragma unroll
+        for (int p = 0; p < SP; ++p)
+          if (on[p]) add(wp[p], t[p]);
+      } else {
+#pragma unroll
+        for (int p = 0; p < SP; ++p) {
+          uint32_t wp, vp, rp;
+          if (pass(p, wp, vp, rp)) add(wp, term(wp, vp, rp));
+        }
       }
     }
   }
@@ -429,15 +454,34 @@ static int pow2_at_least(int s) { return s <= 1 ? 1 : s <= 2 ? 2 : s <= 4 ? 4 : 
 //    them where the outputs allow, so that panels and parts fill 256 compute
 //    units with few parts to add up. More than TB_MAXP panels would leave a
 //    batch only a few records per panel: scattered.
-//  - Small products: the binned form's three kernels take about 35 us a call, as
-//    does a scatter of 2^13 transactions; with more, few output rows take many
-//    atomics each, and those to one address wait for one another (3,000 rows of
-//    30 entries, 8 vectors: 34 us against 118; 5,068 rows of about 26, one
-//    vector: 41 against 76; 1,000 rows of 10, one vector: 32 and 35).
-//  - Large products of one vector and almost only diagonals: adjacent lanes add to
-//    adjacent sums, so eight terms are one transaction and the scatter is cheaper
-//    than records (211,991 rows, 55 diagonals: 82 us against 110). Below 2^22 entries
-//    the records win there too (50,083 rows of 21: 38 us against 44).
+//  - Runs: a workgroup works on a batch's records of its panel as one piece or more,
+//    each a chain of loads that takes as long for one record as for 64, so the
+//    additions take as long as the runs to a workgroup, a scatter as long as its
+//    transactions. Scattered where records by workgroups to a run are fewer than
+//    min_records. Four vectors, 20,000 rows of 300 (each a batch) over 300,000
+//    columns (900): 415 us binned, 271 scattered; over 150,000 (1,800): 249 and 269.
+//    Eight: 200,000 rows of 6 over 300,000 (2,043): 96 and 78; 20,000 of 300 over
+//    60,000 (2,400): 274 and 271, over 20,000 (3,600): 208 and 275. Sixteen: over
+//    150,000 (300): 1,371 and 536, over 60,000 (1,200): 475 and 530. Two: over
+//    1,000,000 (590): 342 and 272, over 300,000 (1,800): 169 and 269. One: over
+//    4,000,000 (300): 256 and 275; 1,000,000 rows with 8 entries in every fiftieth
+//    (163): 39 and 20. Not with fewer tiles than fill the GPU with a scatter's
+//    workgroups (8 vectors, 50,000 rows of 30 over 300,000 columns, 196 tiles, 2,043:
+//    98 and 117).
+//  - Small products: few transactions are soon done, but few output rows take many
+//    atomics each, and those to one address wait for one another, so the line is
+//    low (600 rows of 10, one vector: 14 us scattered, 16 binned, four: 23 and 16; 1,000:
+//    16 and 17, 25 and 16), with five vectors or more lower still (100 rows of 10: 32
+//    and 17; 60: 13 and 11), and for one vector and short columns higher (30,000 rows
+//    of 5 near the diagonal: 15 and 21, all over: 17 and 17; of 12: 20 and 21, 27 and
+//    20; 20,000 rows of 12 over 1,000,000 columns: 24 and 29).
+//  - Almost only diagonals: adjacent lanes add to adjacent sums, so a transaction
+//    takes 8 / SP of them, and atomics to one address are few. Scattered up to
+//    max_per_row transactions to an output row: one vector always (200,000 rows, 40
+//    diagonals: 61 us scattered, 78 binned; 5: 16 and 31), two vectors up to 32
+//    diagonals (100,000 rows, 21: 37 and 47; 40: 61 and 60), four up to 10 (200,000
+//    rows, 5: 35 and 39; 9: 57 and 57; 21: 114 and 78), more never (eight, 400,000
+//    rows, 3: 70 and 56; 5: 108 and 72).
 //  - Scratch: the records of all entries, at most TB_MAX_SCRATCH.
 struct TPlan {
   bool ok = false;
@@ -445,24 +489,29 @@ struct TPlan {
   size_t rec_bytes = 0, off_bytes = 0, part_bytes = 0;
 };
 constexpr size_t TB_MAX_SCRATCH = (size_t)1 << 30;
-constexpr int64_t T_MIN_TRANSACTIONS = (int64_t)1 << 13;
-constexpr int64_t T_MIN_BAND = (int64_t)1 << 22;
+constexpr int64_t T_MIN_TRANSACTIONS = (int64_t)1 << 13, T_MIN_TRANSACTIONS_1 = (int64_t)1 << 18, T_MIN_TRANSACTIONS_8 = 512;
+constexpr uint32_t T_MIN_TILES = 512;
 
 static TPlan t_plan(const DevMat& A, const TransposeInfo& I, int s) {
   TPlan t;
   const int sp = pow2_at_least(s);
   const int64_t n = A.ncols;
   const int64_t transactions = I.nnz * ((s + 7) / 8);
-  if (!I.nbatch || transactions < T_MIN_TRANSACTIONS) return t;
-  if (s == 1 && I.nnz >= T_MIN_BAND && I.nnz - I.nband + I.nband / 8 < I.nnz / 5) return t;
+  if (!I.nbatch || transactions < (sp >= 8 ? T_MIN_TRANSACTIONS_8 : T_MIN_TRANSACTIONS)) return t;
+  if (s == 1 && I.nnz < T_MIN_TRANSACTIONS_1 && I.nnz <= 12 * n) return t;
+  const int64_t max_per_row = sp <= 2 ? 8 : sp == 4 ? 5 : 0, rest = I.nnz - I.nband;
+  if (rest < I.nnz / 10 && I.nband * sp / 8 + rest * ((s + 7) / 8) <= max_per_row * n) return t;
   uint32_t top = 14;
   for (int k = 1; k < sp; k *= 2) --top;
   t.sh = 6;
   while (t.sh < top && (n + ((int64_t)1 << t.sh) - 1) >> t.sh > 32) ++t.sh;
   const int64_t P = (n + ((int64_t)1 << t.sh) - 1) >> t.sh;
   if (P > TB_MAXP) return t;
+  const int64_t Q = std::min<int64_t>({16, std::max<int64_t>(1, 256 / P), I.nbatch});
+  const int64_t min_records = sp == 1 ? 250 : sp == 2 ? 1000 : sp == 4 ? 1700 : sp == 8 ? 2400 : 900;
+  if (A.ntiles >= T_MIN_TILES && I.nnz * P * Q < min_records * I.runs[t.sh]) return t;
   t.P = (uint32_t)P;
-  t.Q = (uint32_t)std::min<int64_t>({16, std::max<int64_t>(1, 256 / P), I.nbatch});
+  t.Q = (uint32_t)Q;
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
   t.rec_bytes = al((size_t)I.nrec * sizeof(uint2));
   t.off_bytes = al((size_t)I.nbatch * (t.P + 1) * sizeof(uint16_t));
