@@ -109,12 +109,12 @@ __device__ inline uint32_t slot_row(const DevMat& A, const Tile& T, uint32_t slo
 
 // ------------------------------------------------------------- scattered ---
 // Lane (e, c) of a wave adds component c of entry e, SP lanes per entry (SP a
-// power of two >= s); the sums of output row j are acc[j*SP .. j*SP + s), so
-// that the SP lanes of an entry make one transaction (SP <= 8). Random rows of
+// power of two >= s); the sums of output row j are acc[j*st .. j*st + s), with
+// st = SP so that the SP lanes of an entry make one transaction (SP <= 8). Random rows of
 // four 64-bit sums take 92 G additions/s this way and 23 G/s when one lane
 // adds the four in turn.
 template <int K, typename Tv, int SP>
-__global__ __launch_bounds__(TILE_THREADS) void k_scatter_t(DevMat A, const Tv* __restrict__ X, int64_t ldx, int s,
+__global__ __launch_bounds__(TILE_THREADS) void k_scatter_t(DevMat A, const Tv* __restrict__ X, int64_t ldx, int s, int st,
                                                             unsigned long long* __restrict__ acc) {
   __shared__ uint32_t rps[TILE_THREADS];
   const Tile T = A.tiles[blockIdx.x];
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(TILE_THREADS) void k_scatter_t(DevMat A, const Tv* 
         return tterm<K>(tvalue(wp, vp, A.m), (uint32_t)X[(int64_t)rp * ldx + comp], A);
       };
       auto add = [&](uint32_t wp, uint32_t t) {
-        atomicAdd(&acc[(int64_t)(wp & COL_MASK) * SP + comp], (unsigned long long)t);
+        atomicAdd(&acc[(int64_t)(wp & COL_MASK) * st + comp], (unsigned long long)t);
       };
       if constexpr (SP <= 4) {
         // every pass's load of x before the first atomic, which would keep it behind (300 rows of 10, 3 vectors: 27 us,
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(TILE_THREADS) void k_scatter_t(DevMat A, const Tv* 
 #pragma unroll
       for (uint32_t d = 0; d < DB; ++d)
         if (v[d])  // an absent entry may lie outside the matrix
-          atomicAdd(&acc[((int64_t)row + A.boffs[T.boff + d0 + d]) * SP + comp], (unsigned long long)tterm<K>(v[d], x, A));
+          atomicAdd(&acc[((int64_t)row + A.boffs[T.boff + d0 + d]) * st + comp], (unsigned long long)tterm<K>(v[d], x, A));
     }
   }
 }
@@ -559,27 +559,34 @@ static hipError_t launch_binned(const DevMat& A, const TransposeInfo& I, const T
                         st);
 }
 
+// Sums to an output row of the scatter: padded to SP, up to T_MAX_PADDED bytes of them; s in larger temporaries,
+// where an output row's sums may lie in one 64-byte piece more (4,000,000 columns of 9 vectors: 288 MB and not 512).
+constexpr size_t T_MAX_PADDED = (size_t)256 << 20;
+static int sum_stride(const DevMat& A, int s) {
+  return (size_t)A.ncols * pow2_at_least(s) * sizeof(uint64_t) <= T_MAX_PADDED ? pow2_at_least(s) : s;
+}
+
 template <int K, typename Tv>
 static hipError_t launch_scattered(const DevMat& A, const Tv* X, int64_t ldx, Tv* Y, int64_t ldy, int s,
                                    uint32_t alpha, uint32_t beta, unsigned long long* acc, hipStream_t st) {
-  const int sp = pow2_at_least(s);
-  const int64_t n = A.ncols, total = n * sp;
+  const int sp = pow2_at_least(s), stride = sum_stride(A, s);
+  const int64_t n = A.ncols, total = n * stride;
   const int zb = (int)std::min<int64_t>((total + 255) / 256, 8192);
   hipLaunchKernelGGL(k_zero_u64, dim3(zb), dim3(256), 0, st, acc, total);
   const dim3 g(A.ntiles), b(TILE_THREADS);
   if (A.ntiles) switch (sp) {
-    case 1: hipLaunchKernelGGL((k_scatter_t<K, Tv, 1>), g, b, 0, st, A, X, ldx, s, acc); break;
-    case 2: hipLaunchKernelGGL((k_scatter_t<K, Tv, 2>), g, b, 0, st, A, X, ldx, s, acc); break;
-    case 4: hipLaunchKernelGGL((k_scatter_t<K, Tv, 4>), g, b, 0, st, A, X, ldx, s, acc); break;
-    case 8: hipLaunchKernelGGL((k_scatter_t<K, Tv, 8>), g, b, 0, st, A, X, ldx, s, acc); break;
-    default: hipLaunchKernelGGL((k_scatter_t<K, Tv, 16>), g, b, 0, st, A, X, ldx, s, acc); break;
+    case 1: hipLaunchKernelGGL((k_scatter_t<K, Tv, 1>), g, b, 0, st, A, X, ldx, s, stride, acc); break;
+    case 2: hipLaunchKernelGGL((k_scatter_t<K, Tv, 2>), g, b, 0, st, A, X, ldx, s, stride, acc); break;
+    case 4: hipLaunchKernelGGL((k_scatter_t<K, Tv, 4>), g, b, 0, st, A, X, ldx, s, stride, acc); break;
+    case 8: hipLaunchKernelGGL((k_scatter_t<K, Tv, 8>), g, b, 0, st, A, X, ldx, s, stride, acc); break;
+    default: hipLaunchKernelGGL((k_scatter_t<K, Tv, 16>), g, b, 0, st, A, X, ldx, s, stride, acc); break;
   }
-  hipLaunchKernelGGL(k_finish_t<Tv>, dim3(zb), dim3(256), 0, st, A, acc, n, s, sp, alpha, beta, Y, ldy);
+  hipLaunchKernelGGL(k_finish_t<Tv>, dim3(zb), dim3(256), 0, st, A, acc, n, s, stride, alpha, beta, Y, ldy);
   return hipGetLastError();
 }
 
 size_t transpose_scratch_bytes(const DevMat& A, const TransposeInfo& I, int s, bool binned) {
-  if (!binned) return (size_t)A.ncols * pow2_at_least(s) * sizeof(uint64_t);
+  if (!binned) return (size_t)A.ncols * sum_stride(A, s) * sizeof(uint64_t);
   const TPlan t = t_plan(A, I, s);
   return t.ok ? t.rec_bytes + t.off_bytes + t.part_bytes : 0;
 }

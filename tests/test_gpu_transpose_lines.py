@@ -91,3 +91,21 @@ def test_short_runs(dev, s, ncols, binned):
 def test_small(dev, s, n, k, binned):
     """Both sides of the lines by transactions (the pool gives the smallest products' memory in one block)."""
     check(dev, uniform(n, n, k), s, binned)
+
+
+@pytest.mark.parametrize("s", [3, 5, 9, 11, 15, 16])
+def test_large_sums_are_packed(dev, s):
+    """A scatter's temporary above 256 MiB holds s sums to an output row, not a power of two."""
+    from paper_1004_3719_amd import Matrix
+    ncols = (1 << 25) // (1 << (s - 1).bit_length()) + 1
+    A = uniform(3000, ncols, 9, m=M31)
+    A.col[:5] = [0, 1, ncols - 3, ncols - 2, ncols - 1]
+    M = Matrix.from_synth(A)
+    X = synth.vector(52, s, A.nrows * s, 0, A.m - 1).reshape(A.nrows, s)
+    Xd = torch.from_numpy(X).to(dev)
+    Y = torch.empty((ncols, s), dtype=torch.int64, device=dev)
+    used = pool_bytes(lambda: M.spmm_t(Xd, Y=Y))
+    print("[case] packed", s, ncols, used, flush=True)
+    assert np.array_equal(Y.cpu().numpy(), oracle.get().spmm_t(A, X))
+    M.close()
+    assert used <= 8 * ncols * s + 4096
