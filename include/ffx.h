@@ -227,7 +227,10 @@ ffx_status ffx_spmv(ffx_matrix A, uint32_t alpha, const void* x, uint32_t beta, 
  * Uses the stored A^T when the handle has one, else the column-sorted groups
  * when it has those, else records of A's entries binned by output rows in a
  * temporary of at most 1 GiB, or a scatter with 64-bit integer atomics where
- * that would not pay or cannot be had: all exact, in any order. */
+ * that would not pay or cannot be had: all exact, in any order. A temporary
+ * comes from the device's stream-ordered pool and returns to it; the pool keeps
+ * it for later calls until the handle is destroyed, when the pool is trimmed to
+ * 64 MiB. */
 ffx_status ffx_spmv_t(ffx_matrix A, uint32_t alpha, const void* x, uint32_t beta, void* y, ffx_dtype dtype,
                       void* stream);
 

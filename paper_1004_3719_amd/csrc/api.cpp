@@ -112,6 +112,15 @@ static void warm_pool(hipStream_t st) {
   (void)st;
 }
 
+// What the pool keeps when the temporaries of transposed products (up to 1 GiB each) are given back.
+constexpr size_t POOL_KEEP = (size_t)64 << 20;
+static void give_back_pool() {
+  int dev = 0;
+  hipMemPool_t pool;
+  if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess)
+    (void)hipMemPoolTrimTo(pool, POOL_KEEP);
+}
+
 // Delayed-reduction bound (Section 2.2): the number of terms that can be
 // added to a reduced accumulator while every partial sum stays exact.
 // Canonical operands lie in [0, m-1]: a term is at most (m-1)^2 (or m, the
@@ -438,6 +447,7 @@ static void product(ffx_matrix M, bool trans, int s, uint32_t alpha, const void*
   // with 64-bit integer atomics into a temporary
   auto scatter = [&](const void* xs, int64_t ldxs, void* ys, int64_t ldys) {
     warm_pool(st);
+    M->t_temporary.store(true, std::memory_order_relaxed);
     if (s == 1 && M->sg.ngroups) {  // one vector on a handle with column-sorted groups
       void* part = nullptr;
       const size_t sg_bytes = sg_transpose_scratch(M->sg.dm);
@@ -610,6 +620,7 @@ ffx_status ffx_matrix_destroy(ffx_matrix A) {
     A->AT.release();
     A->sg.release();
     if (A->perm) (void)hipFree(A->perm);
+    if (A->t_temporary.load(std::memory_order_relaxed)) give_back_pool();  // the frees above waited for the products
     delete A;
   });
 }

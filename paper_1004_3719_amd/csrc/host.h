@@ -3,6 +3,7 @@
 
 #include <stdint.h>
 
+#include <atomic>
 #include <mutex>
 #include <new>
 #include <string>
@@ -170,6 +171,7 @@ struct ffx_matrix_s {
   bool has_t = false;
   // reordered matrices: A and AT hold P A P^T; perm[new] = old on the device
   uint32_t* perm = nullptr;
+  std::atomic<bool> t_temporary{false};  // a transposed product took a temporary from the device's pool
   ffx_matrix_info info{};
   // The temporary of the row products (x in 16 bits and/or in the stored order), allocated on the
   // first product that needs one and kept until destroy: a stream-ordered allocation per product

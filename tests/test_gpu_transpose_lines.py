@@ -14,7 +14,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 M31 = 2**31 - 1
-USED_HIGH = 8  # hipMemPoolAttrUsedMemHigh
+RESERVED, USED_HIGH = 5, 8  # hipMemPoolAttrReservedMemCurrent, hipMemPoolAttrUsedMemHigh
 
 
 @pytest.fixture(scope="module")
@@ -109,3 +109,34 @@ def test_large_sums_are_packed(dev, s):
     assert np.array_equal(Y.cpu().numpy(), oracle.get().spmm_t(A, X))
     M.close()
     assert used <= 8 * ncols * s + 4096
+
+
+@pytest.mark.parametrize("s,opts", [(1, {"col_sorted": 0}), (1, {"col_sorted": 1}), (4, {"col_sorted": 0})])
+def test_temporary_is_given_back(dev, s, opts):
+    """The pool keeps a transposed product's temporary while the handle lives, and at most 64 MiB after it."""
+    from paper_1004_3719_amd import Matrix
+    hip = ctypes.CDLL("libamdhip64.so")
+    pool, v = ctypes.c_void_p(), ctypes.c_uint64(0)
+    torch.cuda.synchronize()
+    assert hip.hipDeviceGetDefaultMemPool(ctypes.byref(pool), 0) == 0
+    assert hip.hipMemPoolTrimTo(pool, ctypes.c_size_t(0)) == 0
+
+    def reserved():
+        assert hip.hipMemPoolGetAttribute(pool, RESERVED, ctypes.byref(v)) == 0
+        return v.value
+
+    before = reserved()
+    A = uniform(400_000, 400_000, 25)
+    M = Matrix.from_synth(A, **opts)
+    X = torch.ones((A.nrows, s), dtype=torch.int32, device=dev)
+    Y = M.spmm_t(X)
+    torch.cuda.synchronize()
+    held = reserved()
+    Z = M.spmm_t(X)  # from what the pool kept
+    torch.cuda.synchronize()
+    assert torch.equal(Y, Z) and reserved() == held
+    M.close()
+    print("[case] pool", s, opts, before, held, reserved(), flush=True)
+    assert reserved() <= max(before, 64 << 20)
+    if not opts["col_sorted"]:
+        assert held > 64 << 20
