@@ -5,7 +5,7 @@
 // order of lists sorted by decreasing estimated cost (longest-processing-
 // time first), so large tiles start early and small ones fill the tail. The
 // counters are cleared by a one-thread kernel before the launch (no memset),
-// and the launches can be captured into a hipGraph and replayed.
+// and the launches can be put into a hipGraph and replayed.
 //
 // XCD-affine queues: MI355X has 8 XCDs, each with its own L2, and hands out
 // consecutive workgroups to the XCDs in turn. With `xcd` set, the matrices are
@@ -24,6 +24,7 @@
 #include <cstring>
 #include <fstream>
 #include <sstream>
+#include <tuple>
 #include <type_traits>
 
 #include "host.h"
@@ -155,11 +156,38 @@ static size_t batch_lds(int64_t mtr, int64_t mte, int sc) {  // at most 53 KB (2
   return a < 16 ? 16 : a;
 }
 
+// Where the launches go: to a stream, or as nodes into a graph, after the node `after` (null: first). The graph is
+// put together node by node because a capture takes a stream and an event per branch, about 25 us each, on the
+// first call of a batch (one class of items: 373 us with eight of each, 306 with four, 77 now; eight
+// classes: 635, now 350).
+struct LaunchTo {
+  hipStream_t st = nullptr;
+  hipGraph_t graph = nullptr;
+  hipGraphNode_t after = nullptr, node = nullptr;  // node: the last one added
+  template <typename... P, typename... A>
+  hipError_t operator()(void (*k)(P...), dim3 grid, dim3 block, size_t lds, A... args) {
+    std::tuple<std::decay_t<P>...> v(args...);
+    return std::apply(
+        [&](auto&... x) -> hipError_t {
+          void* p[] = {(void*)&x...};
+          if (!graph) return hipLaunchKernel((const void*)k, grid, block, p, lds, st);
+          hipKernelNodeParams n{};
+          n.func = (void*)k;
+          n.gridDim = grid;
+          n.blockDim = block;
+          n.sharedMemBytes = (unsigned)lds;
+          n.kernelParams = p;
+          return hipGraphAddKernelNode(&node, graph, after ? &after : nullptr, after ? 1 : 0, &n);
+        },
+        v);
+  }
+};
+
 // One class's persistent launch over its items (qinfo: the class's queue table, counter: its NQ counters).
 static hipError_t batch_launch_class(int ak, ffx_dtype dt, bool x16, int cls, const DevMat* mats,
                                      const BatchOperand* ops, const BatchItem* items, const uint32_t* qinfo,
-                                     uint32_t* counter, int grid, int64_t mtr, int64_t mte,
-                                     hipStream_t st) {
+                                     uint32_t* counter, int grid, int64_t mtr, int64_t mte, LaunchTo& to) {
+  hipError_t e = hipSuccess;
   auto go = [&](auto ar) {
     using AR = decltype(ar);
     auto launch = [&](auto tx, auto tv, auto scv) {
@@ -167,11 +195,10 @@ static hipError_t batch_launch_class(int ak, ffx_dtype dt, bool x16, int cls, co
       using Tv = decltype(tv);
       constexpr int SC = decltype(scv)::value;
       if (cls & 1)
-        hipLaunchKernelGGL((k_batch<AR, Tx, Tv, SC, true>), dim3(grid), dim3(TILE_THREADS), 0, st, mats, ops, items, qinfo,
-                           counter);
+        e = to(k_batch<AR, Tx, Tv, SC, true>, dim3(grid), dim3(TILE_THREADS), 0, mats, ops, items, qinfo, counter);
       else
-        hipLaunchKernelGGL((k_batch<AR, Tx, Tv, SC, false>), dim3(grid), dim3(TILE_THREADS), batch_lds<AR>(mtr, mte, SC),
-                           st, mats, ops, items, qinfo, counter);
+        e = to(k_batch<AR, Tx, Tv, SC, false>, dim3(grid), dim3(TILE_THREADS), batch_lds<AR>(mtr, mte, SC), mats, ops,
+               items, qinfo, counter);
     };
     auto by_dt = [&](auto scv) {
       // the 16-bit gathers are built for the integer class of m <= 65536 only
@@ -210,7 +237,7 @@ static hipError_t batch_launch_class(int ak, ffx_dtype dt, bool x16, int cls, co
     case AK_F64C_32: go(ArCentered<double, uint32_t, false>{}); break;
     default: go(ArCentered<double, uint32_t, true>{}); break;
   }
-  return hipGetLastError();
+  return e;
 }
 
 }  // namespace ffx
@@ -367,53 +394,33 @@ static void batch_run(ffx_batch_s* B, const void* const* X, const int64_t* ldx, 
   FFX_HIP(hipMemcpyAsync(B->d_ops, B->h_ops.data(), B->h_ops.size() * sizeof(BatchOperand), hipMemcpyHostToDevice, st));
   const int wpc = B->params.wg_per_cu ? B->params.wg_per_cu : 4;
   auto grid_of = [&](int c) { return (int)std::min<int64_t>((int64_t)B->ncu * wpc, B->cls_n[c]); };
-  auto launch_class = [&](int c, hipStream_t s) {
+  auto launch_class = [&](int c, LaunchTo& to) {
     return batch_launch_class(B->ak, dt, x16, c, B->d_mats, B->d_ops, B->d_items + B->cls_first[c],
-                              B->d_qinfo + c * 2 * NQ, B->d_counter + c * NQ, grid_of(c), B->mtr, B->mte, s);
+                              B->d_qinfo + c * 2 * NQ, B->d_counter + c * NQ, grid_of(c), B->mtr, B->mte, to);
   };
-  auto launch_x16 = [&](hipStream_t s) -> hipError_t {
-    if (!x16) return hipSuccess;
-    if (dt == FFX_I32) hipLaunchKernelGGL(k_batch_x16<int32_t>, dim3(64, B->count), dim3(256), 0, s, B->d_ops);
-    else hipLaunchKernelGGL(k_batch_x16<int64_t>, dim3(64, B->count), dim3(256), 0, s, B->d_ops);
-    return hipGetLastError();
+  // the counters are cleared, then X is copied to 16 bits, then the classes run: one after another on a stream, and
+  // as independent branches of a graph, where their kernels share the GPU and their tails overlap
+  auto launch_all = [&](LaunchTo& to) -> hipError_t {
+    hipError_t e = to(k_batch_reset, dim3(1), dim3(64), 0, B->d_counter, NCLS * NQ);
+    to.after = to.node;
+    if (e == hipSuccess && x16) {
+      const dim3 g(64, B->count), b(256);
+      e = dt == FFX_I32 ? to(k_batch_x16<int32_t>, g, b, 0, B->d_ops) : to(k_batch_x16<int64_t>, g, b, 0, B->d_ops);
+      to.after = to.node;
+    }
+    for (int c = NCLS - 1; c >= 0 && e == hipSuccess; --c)  // the widest, whose items take longest, first
+      if (B->cls_n[c]) e = launch_class(c, to);
+    return e;
   };
+  LaunchTo to;
   if (B->params.use_graph) {
     if (B->exec && B->graph_dt != (int)dt) B->drop_graph();
     if (!B->exec) {
-      // the classes are independent branches of one graph: their kernels share the GPU and their
-      // tails overlap
       B->graph_dt = (int)dt;
-      hipStream_t cs, br[NCLS] = {};
-      hipEvent_t ev0 = nullptr, evc[NCLS] = {};
-      FFX_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-      hipError_t e = hipSuccess;
-      for (int c = 0; c < NCLS && e == hipSuccess; ++c) {
-        e = hipStreamCreateWithFlags(&br[c], hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&evc[c], hipEventDisableTiming);
-      }
-      if (e == hipSuccess) e = hipEventCreateWithFlags(&ev0, hipEventDisableTiming);
-      if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-      if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, cs, B->d_counter, NCLS * NQ);
-        hipError_t le = launch_x16(cs);
-        if (le == hipSuccess) le = hipEventRecord(ev0, cs);
-        for (int c = NCLS - 1; c >= 0 && le == hipSuccess; --c) {  // the widest, whose items take longest, first
-          if (!B->cls_n[c]) continue;
-          le = hipStreamWaitEvent(br[c], ev0, 0);
-          if (le == hipSuccess) le = launch_class(c, br[c]);
-          if (le == hipSuccess) le = hipEventRecord(evc[c], br[c]);
-          if (le == hipSuccess) le = hipStreamWaitEvent(cs, evc[c], 0);
-        }
-        e = hipStreamEndCapture(cs, &B->graph);
-        if (e == hipSuccess) e = le;
-      }
+      hipError_t e = hipGraphCreate(&B->graph, 0);
+      to.graph = B->graph;
+      if (e == hipSuccess) e = launch_all(to);
       if (e == hipSuccess) e = hipGraphInstantiate(&B->exec, B->graph, nullptr, nullptr, 0);
-      for (int c = 0; c < NCLS; ++c) {
-        if (evc[c]) (void)hipEventDestroy(evc[c]);
-        if (br[c]) (void)hipStreamDestroy(br[c]);
-      }
-      if (ev0) (void)hipEventDestroy(ev0);
-      (void)hipStreamDestroy(cs);
       if (e != hipSuccess) {
         B->drop_graph();
         FFX_HIP(e);
@@ -422,10 +429,8 @@ static void batch_run(ffx_batch_s* B, const void* const* X, const int64_t* ldx, 
     FFX_HIP(hipGraphLaunch(B->exec, st));
     return;
   }
-  hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, st, B->d_counter, NCLS * NQ);
-  FFX_HIP(launch_x16(st));
-  for (int c = NCLS - 1; c >= 0; --c)
-    if (B->cls_n[c]) FFX_HIP(launch_class(c, st));
+  to.st = st;
+  FFX_HIP(launch_all(to));
 }
 
 
