@@ -198,7 +198,7 @@ static ffx_matrix_s* build(const RCsr& A, uint32_t m, const ffx_build_opts* opts
       int dev = 0, ncu = 0;
       FFX_HIP(hipGetDevice(&dev));
       FFX_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-      encode_sg(S, M->md, ncu, !build_t, max_col, st, &M->sg);
+      encode_sg(S, M->md, po.split_pm1, ncu, !build_t, max_col, st, &M->sg);
       M->sg.dm.rowmap = M->perm;
     }
     M->A.dm.reduce_every = b;

@@ -144,8 +144,9 @@ struct SgEncoded {
 };
 // Encodes A (m <= 65536) in about target_groups groups and uploads it; with the index of the transposed
 // product when `transposed` (max_col: the longest column of A).
-void encode_sg(const RCsr& A, const Modulus& md, int target_groups, bool transposed, int64_t max_col, hipStream_t st,
-               SgEncoded* out);
+// split_pm1: without values where every entry is +-1.
+void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_groups, bool transposed, int64_t max_col,
+               hipStream_t st, SgEncoded* out);
 
 // Learned selector hook: fills fmt for the blocks, returns false to fall back.
 bool learned_formats(const std::string& model_path, const std::vector<BlockStats>& blocks, std::vector<int32_t>& fmt,

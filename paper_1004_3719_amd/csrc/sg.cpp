@@ -20,8 +20,8 @@ struct SgPart {  // one group, encoded from offset 0
   std::vector<uint16_t> val;
 };
 
-// rows [r0, r1) of A: entries sorted by (column, row), cut into chunks of columns within 65,536 of their base
-void encode_group(const RCsr& A, int64_t r0, int64_t r1, SgPart& P) {
+// rows [r0, r1) of A mod m: entries sorted by (column, row), cut into chunks of columns within 65,536 of their base
+void encode_group(const RCsr& A, int64_t r0, int64_t r1, uint32_t m, bool values, SgPart& P) {
   const int64_t k0 = A.rp[r0], k1 = A.rp[r1];
   // key: column (bits 30..59) | row in the group (bits 16..29) | value (bits 0..15)
   std::vector<uint64_t> key((size_t)(k1 - k0));
@@ -30,7 +30,7 @@ void encode_group(const RCsr& A, int64_t r0, int64_t r1, SgPart& P) {
       key[k - k0] = ((uint64_t)A.col[k] << 30) | ((uint64_t)(i - r0) << SG_ROW_SHIFT) | A.val[k];
   std::sort(key.begin(), key.end());
   P.ent.reserve(key.size() + key.size() / 16 + SG_CHUNK);
-  P.val.reserve(P.ent.capacity());
+  if (values) P.val.reserve(P.ent.capacity());
   for (size_t q = 0; q < key.size();) {
     const uint32_t base = (uint32_t)(key[q] >> 30);
     size_t n = 0;  // entries of the chunk
@@ -38,7 +38,7 @@ void encode_group(const RCsr& A, int64_t r0, int64_t r1, SgPart& P) {
     const size_t at = P.ent.size();
     P.cbase.push_back(base);
     P.ent.resize(at + SG_CHUNK);
-    P.val.resize(at + SG_CHUNK);
+    if (values) P.val.resize(at + SG_CHUNK);
     for (size_t t = 0; t < SG_CHUNK; ++t) {
       const uint64_t kk = key[q + std::min(t, n - 1)];
       const bool pad = t >= n;
@@ -46,8 +46,9 @@ void encode_group(const RCsr& A, int64_t r0, int64_t r1, SgPart& P) {
                      row = pad ? (uint32_t)(t % (size_t)(r1 - r0)) & (SG_MAX_ROWS - 1)
                                : (uint32_t)(kk >> SG_ROW_SHIFT) & (SG_MAX_ROWS - 1);
       const size_t w = at + 4 * (t % 64) + t / 64;  // entry 64k + l at place 4l + k
-      P.ent[w] = ((pad ? TAG_PAD : 0u) << TAG_SHIFT) | (row << SG_ROW_SHIFT) | col;
-      P.val[w] = pad ? 0 : (uint16_t)(kk & 0xFFFFu);
+      const uint32_t v = (uint32_t)(kk & 0xFFFFu), tag = pad ? TAG_PAD : v == 1 ? TAG_PLUS : v == m - 1 ? TAG_MINUS : TAG_GEN;
+      P.ent[w] = (tag << TAG_SHIFT) | (row << SG_ROW_SHIFT) | col;
+      if (values) P.val[w] = pad ? 0 : (uint16_t)v;
     }
     q += n;
   }
@@ -55,8 +56,8 @@ void encode_group(const RCsr& A, int64_t r0, int64_t r1, SgPart& P) {
 
 }  // namespace
 
-void encode_sg(const RCsr& A, const Modulus& md, int target_groups, bool transposed, int64_t max_col, hipStream_t st,
-               SgEncoded* out) {
+void encode_sg(const RCsr& A, const Modulus& md, bool split_pm1, int target_groups, bool transposed, int64_t max_col,
+               hipStream_t st, SgEncoded* out) {
   out->release();
   if (!md.small()) fail(FFX_EUNSUPPORTED, "column-sorted groups need m <= 65536");
   const int64_t n = A.nrows, nnz = A.nnz();
@@ -73,9 +74,11 @@ void encode_sg(const RCsr& A, const Modulus& md, int target_groups, bool transpo
     ranges.push_back({r0, r});
   }
   const int64_t G = (int64_t)ranges.size();
+  const bool values =
+      !split_pm1 || !std::all_of(A.val.begin(), A.val.end(), [&](uint32_t v) { return v == 1 || v == md.m - 1; });
   std::vector<SgPart> parts(G);
 #pragma omp parallel for schedule(dynamic, 1)
-  for (int64_t g = 0; g < G; ++g) encode_group(A, ranges[g].first, ranges[g].second, parts[g]);
+  for (int64_t g = 0; g < G; ++g) encode_group(A, ranges[g].first, ranges[g].second, md.m, values, parts[g]);
   std::vector<SgGroup> groups(G);
   size_t nent = 0, nch = 0;
   uint32_t max_rows = 0;
@@ -110,7 +113,7 @@ void encode_sg(const RCsr& A, const Modulus& md, int target_groups, bool transpo
   if (nent >= UINT32_MAX) fail(FFX_EUNSUPPORTED, "column-sorted encoding exceeds 2^32 words");
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
   const size_t o_g = 0, o_e = o_g + al(G * sizeof(SgGroup)), o_v = o_e + al(nent * 4),
-               o_b = o_v + al(nent * 2), o_t = o_b + al(nch * 4),
+               o_b = o_v + (values ? al(nent * 2) : 0), o_t = o_b + al(nch * 4),
                total = std::max<size_t>(256, o_t + al(tindex.size() * sizeof(uint2)));
   std::vector<unsigned char> host(total, 0);
   std::memcpy(host.data() + o_g, groups.data(), G * sizeof(SgGroup));
@@ -118,7 +121,7 @@ void encode_sg(const RCsr& A, const Modulus& md, int target_groups, bool transpo
   for (int64_t g = 0; g < G; ++g) {
     const SgPart& P = parts[g];
     std::memcpy(host.data() + o_e + e * 4, P.ent.data(), P.ent.size() * 4);
-    std::memcpy(host.data() + o_v + e * 2, P.val.data(), P.val.size() * 2);
+    if (values) std::memcpy(host.data() + o_v + e * 2, P.val.data(), P.val.size() * 2);
     std::memcpy(host.data() + o_b + c * 4, P.cbase.data(), P.cbase.size() * 4);
     e += P.ent.size();
     c += P.cbase.size();
@@ -135,7 +138,7 @@ void encode_sg(const RCsr& A, const Modulus& md, int target_groups, bool transpo
   SgMat& M = out->dm;
   M.groups = (const SgGroup*)(d + o_g);
   M.ent = (const uint32_t*)(d + o_e);
-  M.val = (const uint16_t*)(d + o_v);
+  M.val = values ? (const uint16_t*)(d + o_v) : nullptr;
   M.cbase = (const uint32_t*)(d + o_b);
   M.rowmap = nullptr;
   M.tindex = tindex.empty() ? nullptr : (const uint2*)(d + o_t);
@@ -147,7 +150,7 @@ void encode_sg(const RCsr& A, const Modulus& md, int target_groups, bool transpo
   M.mu = md.mu;
   out->ngroups = G;
   out->device_bytes = (int64_t)total;
-  out->stream_bytes = (int64_t)(G * sizeof(SgGroup) + nent * 6 + nch * 4);
+  out->stream_bytes = (int64_t)(G * sizeof(SgGroup) + nent * (values ? 6 : 4) + nch * 4);
 }
 
 }  // namespace ffx

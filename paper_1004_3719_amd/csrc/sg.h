@@ -14,14 +14,16 @@
 // m <= 65536 a term is below 2^32, so no row can overflow 64 bits.
 //
 // Layout. The entries of a group are sorted by column and cut into chunks of
-// 256. Entry word: tag (2 bits, 0 or TAG_PAD) | row in the group (14 bits) |
+// 256. Entry word: tag (2 bits, as in the tiles) | row in the group (14 bits) |
 // column - chunk base (16 bits); a chunk stores its base, its first
 // column, and ends where the next column would not fit. Every entry,
 // +-1 or not, has its 16-bit value at the same place of `val`: a term is then
 // one multiplication whatever the entry, where compacted values took four
 // ballots, the selection of a value from the three words loaded and two
 // branches on the tag per entry, which the kernels spent more time on than the
-// 1.2 bytes per entry they saved (60% of +-1). Entry e of a chunk is taken by
+// 1.2 bytes per entry they saved (60% of +-1; with 97% both take 61 us on 1,500,000
+// power-law rows). Where all entries are +-1 there is no `val`, and the tag says
+// which (modulo 2: 61.1 us with values, 54.0 without). Entry e of a chunk is taken by
 // lane e mod 64 as its e/64-th, so one step covers 64 consecutive sorted
 // columns; the chunk stores entry 64k + l at place 4l + k, so lane l reads its
 // four words with one 16-byte load and its values with one 8-byte load. Padding
@@ -50,7 +52,7 @@ static_assert(sizeof(SgGroup) == 16, "group layout");
 struct SgMat {
   const SgGroup* groups;
   const uint32_t* ent;     // SG_CHUNK words per chunk
-  const uint16_t* val;     // SG_CHUNK values per chunk
+  const uint16_t* val;     // SG_CHUNK values per chunk; null when every entry is +-1
   const uint32_t* cbase;   // per chunk: the column its entries count from
   const uint32_t* rowmap;  // when not null, row r of the product is written to row rowmap[r] of y
   const uint2* tindex;     // [panel][group]: the chunks (relative to the group) with columns of the panel,

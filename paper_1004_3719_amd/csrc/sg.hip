@@ -17,7 +17,9 @@ constexpr size_t SG_LDS_FLOOR = 96 * 1024;
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
-// This lane's four entry words of chunk ch, and their values two to a word (streamed once)
+// This lane's four entry words of chunk ch, and their values two to a word (streamed once); without VALS a value is
+// 1 or m - 1, by the tag
+template <bool VALS>
 struct SgLane {
   uint32_t w[4], p[2];
   __device__ inline void words(const SgMat& G, uint32_t ch, uint32_t lane) {
@@ -28,11 +30,16 @@ struct SgLane {
     w[3] = q.w;
   }
   __device__ inline void values(const SgMat& G, uint32_t ch, uint32_t lane) {
+    if constexpr (!VALS) return;
     const u32x2_t q = __builtin_nontemporal_load((const u32x2_t*)(G.val + (size_t)ch * SG_CHUNK) + lane);
     p[0] = q.x;
     p[1] = q.y;
   }
-  __device__ inline uint32_t val(int k) const { return (k & 1) ? p[k / 2] >> 16 : p[k / 2] & 0xFFFFu; }
+  __device__ inline bool pad(int k) const { return (w[k] >> TAG_SHIFT) == TAG_PAD; }
+  __device__ inline uint32_t val(int k, uint32_t m) const {  // of an entry; 0 for padding with VALS
+    if constexpr (VALS) return (k & 1) ? p[k / 2] >> 16 : p[k / 2] & 0xFFFFu;
+    else return (w[k] >> TAG_SHIFT) == TAG_PLUS ? 1u : m - 1;
+  }
   __device__ inline uint32_t col(int k) const { return w[k] & SG_COL_MASK; }
   __device__ inline uint32_t row(int k) const { return (w[k] >> SG_ROW_SHIFT) & (SG_MAX_ROWS - 1); }
 };
@@ -61,7 +68,7 @@ __device__ inline void sg_write(const SgMat& G, const SgGroup& g, const unsigned
 // compacted values, 80.0 with each entry's loaded. Four chunks in flight instead
 // of two: the same. A wave copying the columns its next 256 or 128 entries span
 // to LDS and gathering from there, four windows ahead: 108 us.
-template <typename Tx, typename Tv, int U, bool GF2>
+template <typename Tx, typename Tv, int U, bool GF2, bool VALS>
 __global__ __launch_bounds__(SG_THREADS) void k_sg(SgMat G, const Tx* __restrict__ x, Tv* __restrict__ y,
                                                    uint32_t alpha, uint32_t beta, uint16_t* __restrict__ y16,
                                                    int64_t ldx, int64_t ldy) {
@@ -77,9 +84,10 @@ __global__ __launch_bounds__(SG_THREADS) void k_sg(SgMat G, const Tx* __restrict
   __syncthreads();
   // the entries of the next U chunks are requested before the gathers of the current ones, so each
   // pass waits on one round trip to memory instead of two
-  SgLane e[U], en[U];
+  using Lane = SgLane<VALS>;
+  Lane e[U], en[U];
   uint32_t cb[U], cbn[U];
-  auto load = [&](uint32_t ch0, SgLane (&q)[U], uint32_t (&c)[U]) {
+  auto load = [&](uint32_t ch0, Lane (&q)[U], uint32_t (&c)[U]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t ch = ch0 + u * NW;
@@ -103,15 +111,15 @@ __global__ __launch_bounds__(SG_THREADS) void k_sg(SgMat G, const Tx* __restrict
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int64_t col = cb[u] + e[u].col(k);
-        xv[u][k] = (e[u].w[k] >> TAG_SHIFT) != TAG_PAD ? (uint32_t)(GF2 ? x[col * ldx] : x[col]) : 0u;
+        xv[u][k] = !e[u].pad(k) ? (uint32_t)(GF2 ? x[col * ldx] : x[col]) : 0u;
       }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        if ((e[u].w[k] >> TAG_SHIFT) != TAG_PAD) {
+        if (!e[u].pad(k)) {
           if constexpr (GF2) atomicXor(&accx[e[u].row(k)], xv[u][k]);  // every entry is 1
-          else atomicAdd(&acc[e[u].row(k)], (unsigned long long)sg_mul(e[u].val(k), xv[u][k]));
+          else atomicAdd(&acc[e[u].row(k)], (unsigned long long)sg_mul(e[u].val(k, G.m), xv[u][k]));
         }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -133,15 +141,23 @@ __global__ __launch_bounds__(SG_THREADS) void k_sg(SgMat G, const Tx* __restrict
 // The largest dynamic LDS a group can ask for: SG_MAX_ROWS 64-bit sums.
 constexpr size_t SG_LDS_MAX = (size_t)SG_MAX_ROWS * 8;
 
-template <typename Tx, typename Tv, bool GF2 = false>
-static hipError_t sg_go(const SgMat& G, const Tx* x, Tv* y, uint32_t alpha, uint32_t beta, uint16_t* y16,
-                        hipStream_t st, int64_t ldx = 1, int64_t ldy = 1) {
+template <typename Tx, typename Tv, bool GF2, bool VALS>
+static hipError_t sg_launch(const SgMat& G, const Tx* x, Tv* y, uint32_t alpha, uint32_t beta, uint16_t* y16,
+                            hipStream_t st, int64_t ldx, int64_t ldy) {
   const size_t lds = std::max<size_t>((size_t)G.max_rows * 8, SG_LDS_FLOOR);
-  auto k = k_sg<Tx, Tv, SG_U, GF2>;
+  auto k = k_sg<Tx, Tv, SG_U, GF2, VALS>;
   hipError_t e = raise_lds_limit((const void*)k, (int)SG_LDS_MAX);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3(G.ngroups), dim3(SG_THREADS), lds, st, G, x, y, alpha, beta, y16, ldx, ldy);
   return hipGetLastError();
+}
+
+template <typename Tx, typename Tv, bool GF2 = false>
+static hipError_t sg_go(const SgMat& G, const Tx* x, Tv* y, uint32_t alpha, uint32_t beta, uint16_t* y16,
+                        hipStream_t st, int64_t ldx = 1, int64_t ldy = 1) {
+  if constexpr (!GF2)
+    if (G.val) return sg_launch<Tx, Tv, false, true>(G, x, y, alpha, beta, y16, st, ldx, ldy);
+  return sg_launch<Tx, Tv, GF2, false>(G, x, y, alpha, beta, y16, st, ldx, ldy);
 }
 
 template <typename Tv>
@@ -183,6 +199,7 @@ constexpr uint32_t SGT_ROUND = 32;         // groups staged at a time, at most
 constexpr int SGT_U = 2;                   // chunks per wave in flight (three or four: the same)
 constexpr size_t SGT_LDS = (((size_t)1 << SGT_SHIFT) + WAVE) * 4 + SGT_XROWS * 2;  // the sums and 64 spare ones
 
+template <bool VALS>
 __global__ __launch_bounds__(SG_THREADS) void k_sg_t(SgMat G, const uint16_t* __restrict__ x16, uint32_t P, uint32_t Q,
                                                      uint32_t slots, uint32_t slot_rows, uint32_t mu32,
                                                      uint32_t* __restrict__ part) {
@@ -216,7 +233,7 @@ __global__ __launch_bounds__(SG_THREADS) void k_sg_t(SgMat G, const uint16_t* __
     const uint32_t total = (uint32_t)__shfl((int)pre, (int)SGT_ROUND - 1);
     pre -= n;  // chunks of the round before this group's
     // the entries of the wave's first chunks are requested before x is staged
-    SgLane e[U];
+    SgLane<VALS> e[U];
     uint32_t cb[U], xo[U];
     auto load = [&](uint32_t j) {
 #pragma unroll
@@ -251,7 +268,8 @@ __global__ __launch_bounds__(SG_THREADS) void k_sg_t(SgMat G, const uint16_t* __
         if (j + u * NW >= total) break;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          uint32_t t = sg_mul(e[u].val(k), xs[xo[u] + e[u].row(k)]);  // below 2^32
+          if (!VALS && e[u].pad(k)) continue;
+          uint32_t t = sg_mul(e[u].val(k, G.m), xs[xo[u] + e[u].row(k)]);  // below 2^32
           t -= __umul24(__umulhi(t, mu32), G.m);  // the quotient is below 2^16 and at most two low: below 3m
           // a column of another panel (below j0 it wraps) goes to the spare sums
           const uint32_t at = min(cb[u] + e[u].col(k), (1u << SGT_SHIFT) + lane);
@@ -293,10 +311,11 @@ hipError_t launch_sg_transpose(const SgMat& G, ffx_dtype dt, const void* x, int6
   uint16_t* x16 = (uint16_t*)scratch;
   uint32_t* part = (uint32_t*)((unsigned char*)scratch + t.x_bytes);
   hipError_t e = launch_compact_x(dt, x, ldx, x16, G.nrows, st);
-  if (e == hipSuccess) e = raise_lds_limit((const void*)k_sg_t, (int)SGT_LDS);
+  auto k = G.val ? k_sg_t<true> : k_sg_t<false>;
+  if (e == hipSuccess) e = raise_lds_limit((const void*)k, (int)SGT_LDS);
   if (e != hipSuccess) return e;
   const uint32_t mu32 = (uint32_t)(((uint64_t)1 << 32) / G.m);
-  hipLaunchKernelGGL(k_sg_t, dim3(t.P * t.Q), dim3(SG_THREADS), SGT_LDS, st, G, x16, t.P, t.Q, t.slots, t.slot_rows,
+  hipLaunchKernelGGL(k, dim3(t.P * t.Q), dim3(SG_THREADS), SGT_LDS, st, G, x16, t.P, t.Q, t.slots, t.slot_rows,
                      mu32, part);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
