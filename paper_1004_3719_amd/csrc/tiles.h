@@ -874,10 +874,19 @@ __device__ inline void stream_tile_1(const DevMat& A, const Tile& T, const Tx* _
   }
 }
 
-// LDS of stream_tile_b for tiles of at most nr rows and ne entries.
+// LDS of stream_tile_b for a tile of nr rows and ne entries: the rows' sums at 0, then the byte offsets of the row
+// starts, the words and the values, which are accessed in sixteens, and the end.
+struct StreamLds {
+  uint32_t rps, words, values, bytes;
+};
 template <class AR, int S>
-__host__ __device__ inline size_t stream_b_lds_bytes(int64_t nr, int64_t ne) {
-  return (size_t)nr * S * sizeof(typename AR::Acc) + (size_t)(nr + 4) / 4 * 16 + (size_t)(ne + 3) / 4 * 32;
+__host__ __device__ inline StreamLds stream_b_lds(uint32_t nr, uint32_t ne) {
+  StreamLds l;
+  l.rps = (nr * S * (uint32_t)sizeof(typename AR::Acc) + 15u) & ~15u;
+  l.words = l.rps + (nr + 4) / 4 * 16;
+  l.values = l.words + (ne + 3) / 4 * 16;
+  l.bytes = l.values + (ne + 3) / 4 * 16;
+  return l;
 }
 
 // s > 1 vectors: words and values are staged in LDS, then each group of S / C
@@ -900,10 +909,11 @@ __device__ inline void stream_tile_m(const DevMat& A, const Tile& T, const Tx* _
   const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
   const uint32_t ne = T.ne, nr = tile_rows(T.kind);
   const uint32_t nchunks = (ne + WCHUNK - 1) / WCHUNK;
-  Acc* rowsum = (Acc*)lds;                          // [nr][S]
-  uint32_t* rps = (uint32_t*)(rowsum + nr * S);     // [nr + 1] tile-relative row starts
-  u32x4* sw = (u32x4*)(rps + (nr + 4) / 4 * 4);     // [ne] words, in fours
-  u32x4* sv = sw + (ne + 3) / 4;                    // [ne] values
+  const StreamLds at = stream_b_lds<AR, S>(nr, ne);
+  Acc* rowsum = (Acc*)lds;                        // [nr][S]
+  uint32_t* rps = (uint32_t*)(lds + at.rps);      // [nr + 1] tile-relative row starts
+  u32x4* sw = (u32x4*)(lds + at.words);           // [ne] words, in fours
+  u32x4* sv = (u32x4*)(lds + at.values);          // [ne] values
   const uint32_t grp = tid / CL, slot = tid % CL * C;
   const RowPiece<C> piece(tid % CL, s);
   for (uint32_t ch = wave; ch < nchunks; ch += NW) {
@@ -1102,10 +1112,10 @@ template <class AR>
 inline size_t tiles_lds_bytes(int64_t max_tile_rows, int64_t max_tile_entries, int S) {
   size_t stream = S == 1 ? TILE_THREADS * sizeof(typename AR::Acc) + (TILE_THREADS + 4) * 4 +
                                (size_t)max_tile_entries * sizeof(typename AR::Prod)
-                  : S == 2  ? stream_b_lds_bytes<AR, 2>(max_tile_rows, max_tile_entries)
-                  : S == 4  ? stream_b_lds_bytes<AR, 4>(max_tile_rows, max_tile_entries)
-                  : S == 8  ? stream_b_lds_bytes<AR, 8>(max_tile_rows, max_tile_entries)
-                            : stream_b_lds_bytes<AR, 16>(max_tile_rows, max_tile_entries);
+                  : S == 2  ? stream_b_lds<AR, 2>((uint32_t)max_tile_rows, (uint32_t)max_tile_entries).bytes
+                  : S == 4  ? stream_b_lds<AR, 4>((uint32_t)max_tile_rows, (uint32_t)max_tile_entries).bytes
+                  : S == 8  ? stream_b_lds<AR, 8>((uint32_t)max_tile_rows, (uint32_t)max_tile_entries).bytes
+                            : stream_b_lds<AR, 16>((uint32_t)max_tile_rows, (uint32_t)max_tile_entries).bytes;
   size_t red = (size_t)(TILE_THREADS / WAVE) * S * sizeof(typename AR::Acc);
   size_t b = stream > red ? stream : red;
   return b < 16 ? 16 : b;
