@@ -226,7 +226,7 @@ template <int K, typename Tv, bool TERM>
 __global__ __launch_bounds__(TILE_THREADS) void k_t_bin(DevMat A, const Tv* __restrict__ X, int64_t ldx, uint32_t sh,
                                                         uint32_t P, uint2* __restrict__ rec,
                                                         uint16_t* __restrict__ off) {
-  __shared__ uint2 srec[TB_MAX];
+  __shared__ __align__(16) uint2 srec[TB_MAX];  // leaves two records to a 16-byte store
   __shared__ uint32_t rps[TILE_THREADS];
   __shared__ uint32_t cnt[TB_MAXP];
   __shared__ uint32_t wsum[TILE_THREADS / WAVE];
