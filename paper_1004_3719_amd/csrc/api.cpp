@@ -6,7 +6,6 @@
 #include <cstring>
 #include <mutex>
 #include <new>
-#include <set>
 #include <utility>
 
 #include "host.h"
@@ -394,15 +393,13 @@ static void* noalloc_scratch_ptr() {
 
 hipError_t raise_lds_limit(const void* k, int bytes) {
   static std::mutex mu;
-  static std::set<std::pair<int, const void*>> done;
+  static LdsLimits limits;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   std::lock_guard<std::mutex> lock(mu);
-  if (done.count({dev, k})) return hipSuccess;
-  e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess) done.insert({dev, k});
-  return e;
+  return limits.raise(dev, k, bytes,
+                      [&] { return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
 }
 
 static void product(ffx_matrix M, bool trans, int s, uint32_t alpha, const void* X, int64_t ldx, uint32_t beta,

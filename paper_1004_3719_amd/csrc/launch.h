@@ -2,6 +2,8 @@
 #pragma once
 
 #include <algorithm>
+#include <map>
+#include <utility>
 
 #include "ffx_impl.h"
 
@@ -112,8 +114,22 @@ hipError_t launch_transpose(const DevMat& A, const TransposeInfo& I, ffx_dtype d
 hipError_t launch_t_parts(ffx_dtype dt, uint32_t m, uint64_t mu, int64_t n, const uint32_t* part, uint32_t Q, int s,
                           int sp, uint32_t alpha, uint32_t beta, void* Y, int64_t ldy, hipStream_t st);
 
-// Raises the dynamic LDS limit of kernel k on the current device, once per kernel and device (a host
-// call that would otherwise cost a few microseconds per launch).
+// The dynamic LDS granted to each kernel on each device so far: the host call that raises it costs a few
+// microseconds, so it is made only for more than that.
+class LdsLimits {
+  std::map<std::pair<int, const void*>, int> granted_;
+
+ public:
+  template <class F>  // set(): makes the host call
+  hipError_t raise(int dev, const void* k, int bytes, F&& set) {
+    int& have = granted_[{dev, k}];
+    if (have >= bytes) return hipSuccess;
+    const hipError_t e = set();
+    if (e == hipSuccess) have = bytes;
+    return e;
+  }
+};
+// Raises the dynamic LDS limit of kernel k on the current device to at least `bytes`.
 hipError_t raise_lds_limit(const void* k, int bytes);
 
 // *first = the smallest flat index k*ldx + c of an entry of the n x s block X

@@ -491,8 +491,12 @@ static hipError_t seq_go(const DevMat& A, int64_t mte, const SeqArgs& q, int bat
   const size_t h8_lds = 4 * 512 * sizeof(uint32_t) + TILE_THREADS * sizeof(uint64_t);
   if (h8 && lds < h8_lds) lds = h8_lds;
   if (lds > 64 * 1024) {  // s > 8 on STREAM tiles of 4,096 entries and 256 rows
-    hipError_t e = raise_lds_limit((const void*)k_seq_step<AR, Ts, 16, ONLY_SELL>,
-                                   (int)tiles_lds_bytes<AR>(TILE_THREADS, 4096, 16));
+    const void* k = S == 2   ? (const void*)k_seq_step<AR, Ts, 2, ONLY_SELL>
+                    : S == 4 ? (const void*)k_seq_step<AR, Ts, 4, ONLY_SELL>
+                    : h8     ? (const void*)k_seq_step_h8<AR, Ts, ONLY_SELL>
+                    : S == 8 ? (const void*)k_seq_step<AR, Ts, 8, ONLY_SELL>
+                             : (const void*)k_seq_step<AR, Ts, 16, ONLY_SELL>;
+    hipError_t e = raise_lds_limit(k, (int)lds);
     if (e != hipSuccess) return e;
   }
   int64_t* base = const_cast<int64_t*>(q.base);

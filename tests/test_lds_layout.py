@@ -39,17 +39,41 @@ int main() {
 """
 
 
+LIMITS = r"""
+#include <cstdio>
+#include "launch.h"
+using namespace ffx;
+int main() {
+  LdsLimits l;
+  int calls = 0, a, b;
+  auto raise = [&](int dev, const void* k, int bytes, hipError_t result) {
+    return l.raise(dev, k, bytes, [&] { ++calls; return result; });
+  };
+  bool ok = raise(0, &a, 70000, hipSuccess) == hipSuccess && calls == 1;
+  ok = ok && raise(0, &a, 70000, hipSuccess) == hipSuccess && raise(0, &a, 66000, hipSuccess) == hipSuccess && calls == 1;
+  ok = ok && raise(0, &a, 150000, hipSuccess) == hipSuccess && calls == 2;  // more than was granted
+  ok = ok && raise(1, &a, 70000, hipSuccess) == hipSuccess && calls == 3;   // another device
+  ok = ok && raise(0, &b, 70000, hipErrorInvalidValue) != hipSuccess && calls == 4;
+  ok = ok && raise(0, &b, 70000, hipSuccess) == hipSuccess && calls == 5;   // a refused call granted nothing
+  printf("%d calls\n", calls);
+  return ok ? 0 : 1;
+}
+"""
+
+
 @pytest.mark.skipif(not shutil.which(HIPCC), reason="no hipcc")
-def test_stream_tile_parts(tmp_path):
-    src, exe = tmp_path / "layout.hip", tmp_path / "layout"
-    src.write_text(SOURCE)
+@pytest.mark.parametrize("name,source", [("layout", SOURCE), ("limits", LIMITS)])
+def test_on_the_host(tmp_path, name, source):
+    """`limits`: a kernel's limit is raised again when a launch needs more than was granted."""
+    src, exe = tmp_path / (name + ".hip"), tmp_path / name
+    src.write_text(source)
     csrc = os.path.join(ROOT, "paper_1004_3719_amd", "csrc")
     # the host's half only: no device code is built, and nothing of it is called
-    r = subprocess.run([HIPCC, "--cuda-host-only", "-O0", "-std=c++17", "-I" + csrc, "-I" + os.path.join(ROOT, "include"),
-                        "-c", str(src), "-o", str(tmp_path / "layout.o")], capture_output=True, text=True)
+    r = subprocess.run([HIPCC, "--cuda-host-only", "-O0", "-fPIC", "-std=c++17", "-I" + csrc, "-I" + os.path.join(ROOT, "include"),
+                        "-c", str(src), "-o", str(exe) + ".o"], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
-    r = subprocess.run(["g++", str(tmp_path / "layout.o"), "-o", str(exe), "-L/opt/rocm/lib", "-lamdhip64",
-                        "-Wl,-rpath,/opt/rocm/lib"], capture_output=True, text=True)
+    r = subprocess.run(["g++", str(exe) + ".o", "-o", str(exe), "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"],
+                       capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
