@@ -1045,7 +1045,7 @@ struct SbCtx {
 };
 
 // Workspace of pmbasis: a node's M1, R and M2, and above them, in turn, its halves' and the planes
-// of its products. One allocation for a whole order basis: with four per node, their calls held up
+// of its products where they take the matrix cores. One allocation for a whole order basis: with four per node, their calls held up
 // the launches (16 x 8, order 8,003: 35.8 ms, 29.2 with one).
 struct SbNode {
   size_t m1, r, m2;
@@ -1058,7 +1058,7 @@ static size_t pmbasis_bytes(int m, int n, int64_t sigma) {
   if (sigma <= SB_LEAF) return 0;
   const int64_t s1 = sigma / 2, s2 = sigma - s1;
   const SbNode N(m, n, s1, s2);
-  const size_t planes = std::max(mx_plane_bytes(s1 + 1, s2, n), mx_plane_bytes(s2 + 1, sigma + 1, m));
+  const size_t planes = m < MX_MINQ ? 0 : std::max(mx_plane_bytes(s1 + 1, s2, n), mx_plane_bytes(s2 + 1, sigma + 1, m));
   return N.m1 + N.r + N.m2 + std::max(planes, pmbasis_bytes(m, n, s2));
 }
 
