@@ -24,6 +24,26 @@ def series(dev, m, n, sigma, p):
     return torch.from_numpy(G.astype(np.int32)).to(dev)
 
 
+@pytest.mark.parametrize("p", [M31, 65521])
+def test_four_coefficients_a_lane(dev, p):
+    """Three rows, order 240,000 and no NTT: the last product has 235 tiles of 1,024 coefficients in each of nine
+    entries, enough for the four-per-lane tiles; the basis is the NTT's."""
+    from paper_1004_3719_amd import sigma_basis
+    from paper_1004_3719_amd.ffx import set_ntt_threshold
+    sigma = 240_000
+    print("[case] four a lane", p, flush=True)
+    G = series(dev, 3, 3, sigma, p)
+    want, dw = sigma_basis(G, p, [0, 1, 2])
+    set_ntt_threshold(0)
+    try:
+        got, dg = sigma_basis(G, p, [0, 1, 2])
+    finally:
+        set_ntt_threshold(1024)
+    assert dw == dg and -(-(max(dg) - min(dg)) // 1024) < 3  # degrees close to one another: the last product is full
+    assert max(dg) > 233 * 1024 and 9 * -(-(max(dg) + 1) // 1024) >= 2048
+    assert torch.equal(want, got)
+
+
 @pytest.mark.parametrize("m,n", [(1, 1), (2, 1), (3, 2)])
 def test_few_rows_take_no_planes(dev, m, n):
     """Below four rows no product takes the matrix cores, and the workspace holds no operands for them."""
