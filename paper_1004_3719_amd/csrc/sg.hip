@@ -62,12 +62,17 @@ __device__ inline void sg_write(const SgMat& G, const SgGroup& g, const unsigned
 // GF2: a matrix mod 2 times one bit-packed word per row (32 vectors over GF(2)):
 // x and y are words (stride ldx, ldy), a row's sum is the exclusive or of its
 // columns' words (32-bit LDS sums).
-// Bound by the gathers: one costs the vector cache about 86 cycles here (it
-// serves a lane or so per cycle however few lines the lanes share). On the
+// Bound by the gathers' misses in the vector cache: the texture data path is busy
+// 76% of the kernel and for 53% of it waits for the cache, which has about 73 reads
+// of the L2 in flight, 384 cycles each; the vector ALU is busy 14%, the LDS 16%. (With
+// compacted values the kernel took 50 us with all gathers in a 4 KB table and 86
+// with x.) What would shorten the wait is not known: half as many lines per compute
+// unit, or four chunks in flight instead of two, take the same time. On the
 // 2,000,000-row power-law matrix a product took 85.6 us when the kernel decoded
-// compacted values, 80.0 with each entry's loaded. Four chunks in flight instead
-// of two: the same. A wave copying the columns its next 256 or 128 entries span
-// to LDS and gathering from there, four windows ahead: 108 us.
+// compacted values, 80.0 with each entry's loaded. A wave copying the columns its
+// next 256 or 128 entries span to LDS and gathering from there, four windows ahead:
+// 108 us. Chunks of +-1 entries marked, so that their values are not read: 96.7 (the
+// mark has to be there before the loads, and splits the additions).
 template <typename Tx, typename Tv, int U, bool GF2, bool VALS>
 __global__ __launch_bounds__(SG_THREADS) void k_sg(SgMat G, const Tx* __restrict__ x, Tv* __restrict__ y,
                                                    uint32_t alpha, uint32_t beta, uint16_t* __restrict__ y16,
@@ -191,9 +196,10 @@ hipError_t launch_sg_gf2(const SgMat& G, const uint32_t* X, int64_t ldx, uint32_
 // halves the sums' LDS and leaves room to stage x for about eleven groups.
 // Groups are dealt out to the parts in turn, since a band puts most of a
 // panel's entries in neighbouring groups. Bound by the latency of a round
-// (stage, then three or four chunks per wave). One vector, 1,000,000 power-law
-// rows (17.2 M entries): 167 us through binned records, 86 with compacted values,
-// 75 now.
+// (stage, then three or four chunks per wave): the texture data path is busy 55% of
+// the kernel (waiting 32%), the vector ALU 31%, the LDS 15%. One vector, 1,000,000
+// power-law rows (17.2 M entries): 167 us through binned records, 86 with compacted
+// values, 75 now.
 constexpr uint32_t SGT_XROWS = 44 * 1024;  // staged 16-bit x entries
 constexpr uint32_t SGT_ROUND = 32;         // groups staged at a time, at most
 constexpr int SGT_U = 2;                   // chunks per wave in flight (three or four: the same)

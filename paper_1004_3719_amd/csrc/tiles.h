@@ -25,7 +25,7 @@
 // and reduces modulo m only when the next term could overflow what the type
 // represents exactly (CHUNK variants; the host sets reduce_every from the
 // bound), otherwise once per row. Entries of residue 1 and m-1 carry no value
-// and add x or m - x (Section 2.4, "Taking into account the +-1").
+// (Section 2.4, "Taking into account the +-1"); a term multiplies by 1 or m - 1.
 //
 // Tx is the element type read from X (int32, int64, or a 16-bit copy of x
 // when m <= 65536), Tv the element type of Y.

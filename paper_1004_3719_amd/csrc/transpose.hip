@@ -18,7 +18,8 @@
 //    entry and vector, 44 us binned.
 //  - scattered (k_scatter_t): one 64-bit atomic per entry and vector, with the
 //    s sums of an output row side by side in adjacent lanes, so an entry costs
-//    ceil(s/8) transactions and not s. For small products and very wide ones.
+//    ceil(s/8) transactions and not s. For small products, very wide ones, few
+//    diagonals and batches that leave few records to a panel (t_plan).
 #include <algorithm>
 
 #include "launch.h"
@@ -420,7 +421,7 @@ __global__ __launch_bounds__(TA_THREADS) void k_t_acc(DevMat A, const Tv* __rest
   for (uint32_t i = tid; i < nj * SP; i += TA_THREADS) out[i] = mod_u64(sums[i], A.m, A.mu);
 }
 
-// y from the parts' residues (at most 16 of them, each below 2^31)
+// y from Q parts, each below 2^32 (residues, or the 32-bit sums of the column-sorted groups; Q <= 2^31)
 template <typename Tv>
 __global__ void k_t_parts(uint32_t m, uint64_t mu, int64_t n, const uint32_t* __restrict__ part, uint32_t Q, int s,
                           int sp, uint32_t alpha, uint32_t beta, Tv* __restrict__ Y, int64_t ldy) {
